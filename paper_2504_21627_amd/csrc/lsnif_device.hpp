@@ -342,6 +342,159 @@ __device__ __forceinline__ int walk_voxels(const Geom &g, const VRay &w, const u
     return n;
 }
 
+// Planes of axis a that the line has crossed by parameter T, of the `most` inner
+// planes it meets in order from cell c0: those with t < T, and with `ties` also
+// those with t == T.  A guess from the position at T, corrected by comparing
+// plane parameters (non-decreasing along the ray), so the count does not
+// depend on the guess.
+__device__ __forceinline__ int planes_crossed(const VRay &w, int a, int c0, int most, int V, float T, bool ties)
+{
+    const bool up = w.d[a] > 0.0f;
+    const int st = up ? 1 : -1, first = c0 + (up ? 1 : 0);
+    const float x = __builtin_fminf(__builtin_fmaxf(w.o[a] + T * w.d[a], 0.0f), (float)(V - 1));
+    int i = ((int)x - c0) * st;
+    i = i < 0 ? 0 : (i > most ? most : i);
+    auto crossed = [&](int k) {
+        const float t = plane_t((float)(first + k * st), w.o[a], w.inv[a]);
+        return t < T || (ties && t == T);
+    };
+    while (i < most && crossed(i)) ++i;
+    while (i > 0 && !crossed(i - 1)) --i;
+    return i;
+}
+
+// The walk by G lanes of a wave together (`lane` = 0..G-1 of them): the voxels
+// walk_voxels would list if it had no cap, in any order.  The cell-by-cell walk
+// merges the axes' plane crossings in order of t, ties to the lowest axis, so the
+// cell it enters at the crossing of plane i of axis a, and that cell's place in
+// the walk, follow from counting the other axes' planes crossed before it.  Each
+// lane takes one crossing at a time: of any plane, looking at the one cell entered
+// (CELLS, the shortest chain), or of a brick boundary, stepping through the cells
+// of the brick entered (at most 10) if it holds anything (about half the work).
+// A listed voxel is appended to found[]: its place, then its planes crossed on
+// axes 0 and 1 (12, 10 and 10 bits; c0 and the signs give the cell back).  *count
+// may pass `room`: entries beyond it are dropped.
+struct WalkStart {
+    int c0[3];
+    bool up[3];
+};
+
+template <bool RECHECK, int G, bool CELLS>
+__device__ __forceinline__ void find_voxels(const Geom &g, const VRay &w, int lane, const uint32_t *coarse,
+                                            uint32_t *count, uint32_t *found, uint32_t room, WalkStart &S)
+{
+    const int V = g.V;
+    int n[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        S.c0[a] = start_cell(g, w, a);
+        S.up[a] = w.d[a] > 0.0f;
+        const int most = (w.mov & (1u << a)) ? (S.up[a] ? V - 1 - S.c0[a] : S.c0[a]) : 0;
+        n[a] = most > 0 ? planes_crossed(w, a, S.c0[a], most, V, w.tb, false) : 0;
+    }
+    // the cell entered after k[] crossings, and without CELLS the rest of its brick
+    auto enter = [&](int k0, int k1, int k2) {
+        int k[3] = {k0, k1, k2}, c[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) c[a] = S.c0[a] + (S.up[a] ? k[a] : -k[a]);
+        const uint32_t b = brick_of(g, c);
+        if (!CELLS && !((coarse[b >> 5] >> (b & 31u)) & 1u)) return;
+        const uint64_t mask = g.fine[b];
+        float en[3], ex[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (w.mov & (1u << a)) {
+                cell_span(w, a, c[a], en[a], ex[a]);
+            } else {
+                en[a] = -__builtin_inff();
+                ex[a] = __builtin_inff();
+            }
+        }
+        for (int it = 0; it < (CELLS ? 1 : 10); ++it) {
+            const float tin = __builtin_fmaxf(__builtin_fmaxf(en[0], en[1]), en[2]);
+            const float tout = __builtin_fminf(__builtin_fminf(ex[0], ex[1]), ex[2]);
+            bool keep = fmin2(tout, w.tb) > fmax2(tin, w.ta);
+            if constexpr (RECHECK)
+                if (g.recheck && grazing(tin, tout, w.ta, w.tb)) keep = keep_f64(w, c, V);
+            if (keep && ((mask >> bit_in_brick(c)) & 1ull)) {
+                const uint32_t at = atomicAdd(count, 1u);
+                if (at < room)
+                    found[at] = ((uint32_t)(k[0] + k[1] + k[2]) << 20) | ((uint32_t)k[0] << 10) | (uint32_t)k[1];
+            }
+            if (CELLS || tout >= w.tb) break;
+            bool left = false;
+            const int oa = ex[0] == tout ? 0 : (ex[1] == tout ? 1 : 2);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                if (a != oa) continue;
+                const int nc = c[a] + (S.up[a] ? 1 : -1);
+                left = ((nc ^ c[a]) & ~3) != 0;
+                c[a] = nc;
+                ++k[a];
+                en[a] = ex[a];
+                ex[a] = plane_t((float)(nc + (S.up[a] ? 1 : 0)), w.o[a], w.inv[a]);
+            }
+            if (left) break;
+        }
+    };
+    if (lane == 0) enter(0, 0, 0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        // i: planes of the axis before this one; brick boundaries are every fourth plane
+        constexpr int every = CELLS ? 1 : 4;
+        const int first = CELLS ? 0 : (S.up[a] ? 3 - (S.c0[a] & 3) : S.c0[a] & 3);
+        for (int i = first + every * lane; i < n[a]; i += every * G) {
+            const float T = plane_t((float)(S.c0[a] + (S.up[a] ? i + 1 : -i)), w.o[a], w.inv[a]);
+            int k[3];
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+                k[b] = b == a ? i + 1 : (n[b] ? planes_crossed(w, b, S.c0[b], n[b], V, T, b < a) : 0);
+            enter(k[0], k[1], k[2]);
+        }
+    }
+}
+
+// walk_voxels by one lane, cell by cell: for rays that meet many voxels, whose list
+// is full after a few cells.  (walk_voxels itself keeps part of its state in
+// scratch memory, and a kernel with scratch takes 10 us longer to start.)
+template <bool RECHECK>
+__device__ __forceinline__ int walk_cells(const Geom &g, const VRay &w, const WalkStart &S, uint32_t *list,
+                                          uint32_t stride, int cap)
+{
+    int c[3] = {S.c0[0], S.c0[1], S.c0[2]}, n = 0;
+    float en[3], ex[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (w.mov & (1u << a)) {
+            cell_span(w, a, c[a], en[a], ex[a]);
+        } else {
+            en[a] = -__builtin_inff();
+            ex[a] = __builtin_inff();
+        }
+    }
+    for (int it = 0; it < 3 * g.V; ++it) {
+        const float tin = __builtin_fmaxf(__builtin_fmaxf(en[0], en[1]), en[2]);
+        const float tout = __builtin_fminf(__builtin_fminf(ex[0], ex[1]), ex[2]);
+        bool keep = fmin2(tout, w.tb) > fmax2(tin, w.ta);
+        if constexpr (RECHECK)
+            if (g.recheck && grazing(tin, tout, w.ta, w.tb)) keep = keep_f64(w, c, g.V);
+        if (keep && ((g.fine[brick_of(g, c)] >> bit_in_brick(c)) & 1ull)) {
+            list[(size_t)n * stride] = pack_ijk(c);
+            if (++n == cap) break;
+        }
+        if (tout >= w.tb) break;
+        const int oa = ex[0] == tout ? 0 : (ex[1] == tout ? 1 : 2);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (a != oa) continue;
+            c[a] += S.up[a] ? 1 : -1;
+            en[a] = ex[a];
+            ex[a] = plane_t((float)(c[a] + (S.up[a] ? 1 : 0)), w.o[a], w.inv[a]);
+        }
+    }
+    return n;
+}
+
 // Boundary point h of a listed voxel: even h = where the line enters the
 // voxel, odd h = where it leaves.  The crossing axis takes the face plane
 // itself; other axes are evaluated on the line and clamped into the voxel.

@@ -124,6 +124,7 @@ namespace lsnif {
 struct PairsSetup {
     const Object *first = nullptr;
     int kbm = 1, maxH = 2;
+    uint32_t max_V = 1;     // largest voxel grid of the objects
     uint32_t hot_max = 0;   // largest hot-level LDS footprint of the objects
     bool recheck = false;   // some object re-decides grazing voxels in float64
     uint32_t walk_chunks = 1;   // largest walk_chunks of the objects
