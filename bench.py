@@ -30,11 +30,11 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 MFMA_FP16_PEAK_TFLOPS = 2500.0
 MFMA_FP32_PEAK_TFLOPS = 157.3
-KERNEL = "k_query_mma<_Float16, _Float16, F=2, WIDTH=64, KBM=2, PAIRS=false, HOT=false>"
+KERNEL = "k_query<_Float16, _Float16, F=2, WIDTH=64, PAIRS=false, R=64>"
 
 
-KERNEL_SOURCES = ("lsnif_device.hpp", "lsnif_kernels.hpp", "lsnif_launch.hpp", "k_mma_f16.hip",
-                  "lsnif_host.hip")
+KERNEL_SOURCES = ("lsnif_device.hpp", "lsnif_kernels.hpp", "lsnif_query.hpp", "lsnif_launch.hpp",
+                  "k_query_f16.hip", "lsnif_host.hip")
 
 
 def kernel_source_hash():
@@ -49,11 +49,6 @@ def kernel_source_hash():
 def tuning_key(t):
     """A tuning as the comma list that `--tuning` takes."""
     return ",".join(str(int(t[k])) for k in ("sort_bits", "pair_bits", "hot_lds_bytes", "walk_chunks", "persistent"))
-
-
-def kernel_label(tuning):
-    """The timed query kernel: the persistent grid is a kernel of its own."""
-    return KERNEL.replace("k_query_mma<", "k_query_mma_persist<") if tuning.get("persistent") else KERNEL
 
 
 def stored_traffic(workload, tuning):
@@ -427,7 +422,7 @@ def bench_c1(L, reps=200):
     dt = (time.perf_counter() - t0) / 5
     return {"workload": "c1: icosphere (1,280 triangles), V=32, 8 levels x 2^14 entries x 2 fp32 features, "
                         "MLP 288-64-64-64-9 fp32, 4,096 rays",
-            "path": "fp32 features, fp32 vector-ALU MLP, one wave per ray (k_query_lat)",
+            "path": "fp32 features, fp32 matrix-core MLP (k_query, 16 rays per block)",
             "rays": n, "launches": reps, "value": n * reps / wall / 1e6, "unit": "Mrays/s",
             "p50_ms": float(np.percentile(lat, 50)), "p99_ms": float(np.percentile(lat, 99)),
             "kernel_ms": kern_ms,
@@ -763,7 +758,7 @@ def bench_c2(L, args):
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": stored_traffic("c2-fp16", head["tuning_isolated"]) if "fp16" in paths else None,
-                     "kernel": kernel_label(head["tuning_isolated"]) if "fp16" in paths else "k_query_f32",
+                     "kernel": KERNEL if "fp16" in paths else KERNEL.replace("_Float16", "float"),
                      "alg_bytes_per_launch": alg_bytes, "fresh_points_per_launch": head["fresh"],
                      "bytes_per_point": bpp, "mean_kernel_ms": mean_ms,
                      "points_per_launch": head["points"], "all_points_bytes_per_launch": all_bytes,

@@ -205,10 +205,8 @@ lsnif_status lsnif_object_bytes(lsnif_ctx *ctx, uint32_t object_id, uint64_t *by
  * workspaces).  Calls on one stream are ordered by the stream. */
 
 /* Query n rays (object space) against one object: out[i] answers rays[i].
- * Batches of at most 8,192 rays of a width-64 object with at most 16 levels
- * (FP32 features and MLP with F <= 3, or a matrix-core MLP with F = 2) run
- * one wave per ray instead of one ray per lane (lower latency); a ray's answer
- * is the same bits either way. */
+ * The kernels split small batches more finely (lower latency); a ray's answer
+ * is the same bits whatever its batch. */
 lsnif_status lsnif_query(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray *d_rays,
                          uint32_t n, lsnif_hit *d_out, void *stream);
 
@@ -329,7 +327,7 @@ lsnif_status lsnif_bounce(lsnif_ctx *ctx, const lsnif_ray *d_rays, const lsnif_h
  *
  * Launch parameters of an object that change speed but never a result (a
  * ray's answer does not depend on which rays share its tile or in what order
- * rays run, nor on whether a table entry is read from HBM or from LDS):
+ * rays run):
  *  sort_bits      single-object queries of at least 8192 rays are first sorted
  *                 by direction octant and by the cell of the voxel grid where
  *                 the ray's segment starts, 2^sort_bits cells per axis
@@ -340,9 +338,8 @@ lsnif_status lsnif_bounce(lsnif_ctx *ctx, const lsnif_ray *d_rays, const lsnif_h
  *  pair_bits      the same grouping, 2^pair_bits cells per axis (1..5), or at 6
  *                 by the cell alone (64 cells per axis, no octant), for the
  *                 object's pairs in pair queries, within the object's tiles.
- *  hot_lds_bytes  LDS per workgroup for the object's coarsest levels (0..40960):
- *                 those levels, all of whose used entries fit, are copied into
- *                 LDS by every workgroup and gathered from there.
+ *  hot_lds_bytes  0..40960: kept with the object, without effect (the coarsest
+ *                 levels are not copied into LDS).
  *  walk_chunks    tile ranges (1..16) of a direct or captured query: the voxel
  *                 walk of each range runs on a side stream of the context
  *                 (default priority) ahead of the query kernel, which starts on
@@ -350,22 +347,14 @@ lsnif_status lsnif_bounce(lsnif_ctx *ctx, const lsnif_ray *d_rays, const lsnif_h
  *                 share the GPU.  1 (the default) walks the whole batch first.
  *                 Ranges hold at least 256 tiles; the serving loop always walks
  *                 whole requests.
- *  persistent     0 or 1: with 1, width-64 objects with a matrix-core MLP
- *                 run the query kernel as a persistent grid (as many
- *                 workgroups as the GPU holds at once) whose workgroups on
- *                 each XCD take tiles from that XCD's own contiguous eighth of
- *                 the coherence order, then from the tails of the others, so
- *                 each XCD's L2 serves one region of rays (or one object's
- *                 pairs) at a time; 0 launches one workgroup per tile, dealt to
- *                 the XCDs in runs of 8.  Width-128 and FP32-MLP objects always
- *                 take one workgroup per tile.
- * lsnif_autotune times each candidate (sort_bits 0, 4, 5, 6, 7 x hot_lds_bytes 0,
- * 20480, 40960, then walk_chunks 1, 2, 4, 8, then persistent 0 and 1, each for
- * the best so far) on the
+ *  persistent     0 or 1: kept with the object, without effect (the query
+ *                 kernel launches its tiles in one grid, dealt to the XCDs in
+ *                 runs of 2,048 slots).
+ * lsnif_autotune times each candidate (sort_bits 0, 4, 5, 6, 7, then walk_chunks
+ * 1, 2, 4, 8 for the best so far) on the
  * caller's batch, a warm-up and three timed queries each on a private stream,
  * keeps the fastest for the object and returns it.  lsnif_autotune_pairs does
- * the same for a pair query (pair_bits 2, 3, 4, 5, 6 x hot_lds_bytes, then
- * walk_chunks, then persistent), applying one choice to every object of the context.  Both
+ * the same for a pair query (pair_bits 2, 3, 4, 5, 6, then walk_chunks), applying one choice to every object of the context.  Both
  * overwrite d_out, synchronise the device and, like lsnif_set_tuning, make the
  * context's captured graphs stale.
  */

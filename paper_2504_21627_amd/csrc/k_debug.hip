@@ -1,4 +1,4 @@
-// Instantiations of the float32 vector-ALU query kernel and the debug kernel.
+// The debug kernel.
 #include "lsnif_kernels.hpp"
 #include "lsnif_launch.hpp"
 
@@ -60,50 +60,6 @@ __global__ __launch_bounds__(kBlock) void k_debug(DebugArgs D)
                 for (int b = 0; b < 3; ++b) D.b.weights[base * 3 + b] = wt[b];
         }
     }
-}
-
-
-template <typename TF, int F>
-static void go(const QueryArgs &A, bool pairs, uint32_t grid, hipStream_t s)
-{
-    // voxel lists of H/2 entries per lane (for pairs, H is the largest over the objects)
-    const size_t lists = (size_t)(A.g.H >> 1) * kBlock * sizeof(uint32_t);
-    if (A.width == 128) {   // the paper's default width: no hot-level variant (hot levels change no result)
-        if (pairs) hipLaunchKernelGGL((k_query_f32<TF, F, 128, true, false>), dim3(grid), dim3(kBlock), lists, s, A);
-        else hipLaunchKernelGGL((k_query_f32<TF, F, 128, false, false>), dim3(grid), dim3(kBlock), lists, s, A);
-        return;
-    }
-    const size_t lds = lists + A.hot_lds;
-    // objects with hot levels take the variant that reads them from LDS
-    if constexpr (hot_entries<TF, F>()) {
-        if (A.hot_lds) {
-            if (pairs) hipLaunchKernelGGL((k_query_f32<TF, F, 64, true, true>), dim3(grid), dim3(kBlock), lds, s, A);
-            else hipLaunchKernelGGL((k_query_f32<TF, F, 64, false, true>), dim3(grid), dim3(kBlock), lds, s, A);
-            return;
-        }
-    }
-    if (pairs) hipLaunchKernelGGL((k_query_f32<TF, F, 64, true, false>), dim3(grid), dim3(kBlock), lds, s, A);
-    else hipLaunchKernelGGL((k_query_f32<TF, F, 64, false, false>), dim3(grid), dim3(kBlock), lds, s, A);
-}
-
-hipError_t launch_lat(const QueryArgs &A, int F, uint32_t grid, hipStream_t s)
-{
-    const dim3 blocks(grid * (kBlock / kLatWaves));   // one wave per slot of the grid's tiles
-    if (F == 2) hipLaunchKernelGGL(k_query_lat<2>, blocks, dim3(64 * kLatWaves), 0, s, A);
-    else hipLaunchKernelGGL(k_query_lat<3>, blocks, dim3(64 * kLatWaves), 0, s, A);
-    return hipGetLastError();
-}
-
-hipError_t launch_f32(const QueryArgs &A, int feat_dtype, int F, bool pairs, uint32_t grid, hipStream_t s)
-{
-    if (feat_dtype == LSNIF_FP32) {
-        if (F == 2) go<float, 2>(A, pairs, grid, s); else go<float, 3>(A, pairs, grid, s);
-    } else if (feat_dtype == LSNIF_FP16) {
-        if (F == 2) go<_Float16, 2>(A, pairs, grid, s); else go<_Float16, 3>(A, pairs, grid, s);
-    } else {
-        if (F == 2) go<__bf16, 2>(A, pairs, grid, s); else go<__bf16, 3>(A, pairs, grid, s);
-    }
-    return hipGetLastError();
 }
 
 hipError_t launch_debug(const DebugArgs &D, hipStream_t s)

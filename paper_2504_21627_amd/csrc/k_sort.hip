@@ -15,10 +15,6 @@
 // sort's histogram and scatter take one device-wide atomic per ray, and those
 // atomics, not the bytes moved, set its pace.
 // Every ray's result is independent of the order the rays are processed in.
-#include <map>
-#include <mutex>
-#include <tuple>
-
 #include "lsnif_kernels.hpp"
 #include "lsnif_launch.hpp"
 
@@ -232,42 +228,6 @@ hipError_t launch_exclusive_scan(uint32_t *v, uint32_t n, uint32_t *part, hipStr
     hipLaunchKernelGGL(k_scan_partial, dim3(nblocks), dim3(kBlock), 0, s, v, n, part);
     hipLaunchKernelGGL(k_scan_final, dim3(nblocks), dim3(kBlock), 0, s, v, n, part);
     return hipGetLastError();
-}
-
-__global__ void k_clear_queue(unsigned long long *q)
-{
-    if (threadIdx.x < 8) q[threadIdx.x] = 0ull;
-}
-
-hipError_t launch_clear_queue(unsigned long long *q, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_clear_queue, dim3(1), dim3(64), 0, s, q);
-    return hipGetLastError();
-}
-
-uint32_t persistent_blocks(const void *kernel, size_t lds, uint32_t tiles)
-{
-    static std::mutex mu;
-    static std::map<std::tuple<int, const void *, size_t>, uint32_t> known;
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    uint32_t nb = 0;
-    {
-        std::lock_guard<std::mutex> lk(mu);
-        auto it = known.find({dev, kernel, lds});
-        if (it != known.end()) nb = it->second;
-    }
-    if (!nb) {
-        int per_cu = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, lds) != hipSuccess) per_cu = 1;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 8;
-        nb = (uint32_t)(per_cu > 0 ? per_cu : 1) * (uint32_t)(cus > 0 ? cus : 8);
-        nb = nb < 8 ? 8 : nb / 8 * 8;
-        std::lock_guard<std::mutex> lk(mu);
-        known[{dev, kernel, lds}] = nb;
-    }
-    const uint32_t want = (tiles + 7u) / 8u * 8u;
-    return want < nb ? (want ? want : 8u) : nb;
 }
 
 hipError_t launch_radix_pass(const uint32_t *sk, const uint32_t *sv, uint32_t *dk, uint32_t *dv, uint32_t n,

@@ -349,9 +349,7 @@ lsnif_status lsnif_build(lsnif_ctx *ctx, const lsnif_object_desc *d, uint32_t *o
         }
         if (d->R[l] % d->V == 0) g.aligned_mask |= 1u << l;
     }
-    ob.esz = (uint32_t)(d->F * dtype_size(d->feat_dtype));
-    ob.hot_budget = 0;   // hot levels are off until a tuning asks for them
-    plan_hot_levels(g, ob.esz, ob.hot_budget);
+    ob.hot_budget = 0;
     // an autotune cache entry for this architecture, shape and precision replaces the defaults
     auto cached = ctx->cache.find(cache_key(ctx, ob));
     if (cached != ctx->cache.end()) {
@@ -360,7 +358,6 @@ lsnif_status lsnif_build(lsnif_ctx *ctx, const lsnif_object_desc *d, uint32_t *o
         ob.hot_budget = (uint32_t)cached->second.hot_lds_bytes;
         ob.walk_chunks = (uint32_t)cached->second.walk_chunks;
         ob.persistent = (uint32_t)cached->second.persistent;
-        plan_hot_levels(g, ob.esz, ob.hot_budget);
     }
     // occupancy as 4x4x4 bricks: one 64-bit mask per brick, then one bit per brick
     const int V = d->V, NB = (V + 3) / 4;
@@ -591,33 +588,6 @@ lsnif_status grow_workspace(void *&buf, size_t &have, size_t need)
     return LSNIF_OK;
 }
 
-// Hot levels: the coarsest levels, in order, while all their used slots (plus
-// the spare entry a paired gather may read) fit `budget` bytes of LDS and two
-// blocks still fit a CU (static LDS + voxel lists + hot levels within half of
-// its 160 KiB); 4- and 8-byte entries only.
-void plan_hot_levels(Geom &g, uint32_t esz, uint32_t budget)
-{
-    g.hot_mask = 0;
-    g.hot_bytes = 0;
-    for (int l = 0; l < kMaxLevels; ++l) g.hot_off[l] = g.hot_len[l] = 0;
-    if (esz != 4 && esz != 8) return;
-    const int64_t lds_left = (int64_t)(80 << 10) - (int64_t)sizeof(Shared) - (int64_t)(g.H / 2) * kBlock * 4;
-    const uint32_t cap = (uint32_t)std::max<int64_t>(0, std::min<int64_t>(std::min(budget, kHotLdsBudget), lds_left));
-    const uint64_t T = (uint64_t)1 << g.log2_T;
-    uint32_t off = 0;
-    for (int l = 0; l < g.L; ++l) {
-        const uint64_t side = (uint64_t)g.R[l] + 1;
-        const uint64_t used = (g.dense_mask >> l) & 1u ? side * side * side : T;
-        const uint64_t len = ((used + 1) * esz + 15) / 16 * 16;
-        if (off + len > cap) break;
-        g.hot_mask |= 1u << l;
-        g.hot_off[l] = off;
-        g.hot_len[l] = (uint32_t)len;
-        off += (uint32_t)len;
-    }
-    g.hot_bytes = off;
-}
-
 lsnif_status check_query(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray *d_rays, uint32_t n,
                          lsnif_hit *d_out, const Object *&ob)
 {
@@ -660,12 +630,12 @@ static size_t list_ws_bytes(size_t n_slots, uint32_t cap)
     return al256(n_slots) + al256(n_slots * cap * sizeof(uint32_t));
 }
 
-// The persistent query kernel's 8 tile-queue counters: one 256-byte granule after the lists.
-constexpr size_t kQueueBytes = 256;
+// One spare 256-byte granule after the lists (part of the sizes callers budget for).
+constexpr size_t kSpareBytes = 256;
 
 size_t query_ws_bytes(uint32_t n, uint32_t sort_bits, uint32_t cap)
 {
-    return sort_ws_bytes(n, sort_bits) + list_ws_bytes(n, cap) + kQueueBytes;
+    return sort_ws_bytes(n, sort_bits) + list_ws_bytes(n, cap) + kSpareBytes;
 }
 
 size_t pairs_ws_bytes(uint32_t n_rays, uint32_t n_pairs, uint32_t n_objs, uint32_t cap, uint32_t pair_bits)
@@ -675,7 +645,7 @@ size_t pairs_ws_bytes(uint32_t n_rays, uint32_t n_pairs, uint32_t n_objs, uint32
     return al256((size_t)n_rays * 8) + al256((size_t)n_pairs * sizeof(PairRes)) + al256((size_t)n_pairs * 4) +
            al256(n_slots * 4) + al256(n_slots / kBlock * 4) + 4 * al256((size_t)n_pairs * 4) +
            al256(radix_hist_words(n_pairs) * 4) + al256((size_t)(n_objs + 1) * 4) + al256((size_t)n_objs * 4) +
-           list_ws_bytes(n_slots, cap) + kQueueBytes;
+           list_ws_bytes(n_slots, cap) + kSpareBytes;
 }
 
 // The walk kernel, then the query kernel, over `ntiles` tiles.  With k > 1 tile
@@ -730,7 +700,6 @@ lsnif_status enqueue_query(lsnif_ctx *ctx, const Object &ob, const lsnif_ray *d_
 {
     QueryArgs A{};
     A.g = ob.geom;
-    A.hot_lds = ob.geom.hot_bytes;
     A.width = (uint32_t)ob.width;
     A.m = ob.mlp;
     A.tables = ob.d_tab;
@@ -773,27 +742,13 @@ lsnif_status enqueue_query(lsnif_ctx *ctx, const Object &ob, const lsnif_ray *d_
     char *wl = static_cast<char *>(ws) + sort_bytes;
     A.nvox = reinterpret_cast<uint8_t *>(wl);
     A.lists = reinterpret_cast<uint32_t *>(wl + al256(n));
-    A.queue = reinterpret_cast<unsigned long long *>(wl + list_ws_bytes(n, ob.geom.H >> 1));
-    A.persistent = ob.persistent && !dbg && !gather_sums ? 1u : 0u;
-    const int kbm = ob.mlp.kb_point;
-    // Batches too small to fill the chip with one ray per lane run one wave per ray (width 64,
-    // at most 16 levels; FP32 MLP with FP32 features and F <= 3, or a matrix-core MLP with
-    // F = 2), whichever debug buffers are asked for: the answers are the same bits.
-    const bool small = !gather_sums && n <= kSmallBatchRays && ob.width == 64 && ob.geom.L <= 16 &&
-                       (ob.mlp_dtype == LSNIF_FP32 ? ob.feat_dtype == LSNIF_FP32 && ob.F <= 3
-                                                   : ob.F == 2 && ob.mlp.kb_point <= 2);
     auto query = [&](const QueryArgs &a, uint32_t g) -> hipError_t {
         if (gather_sums) return launch_gather_only(a, ob.feat_dtype, ob.F, gather_sums, g, s);
-        if (small) {
-            if (ob.mlp_dtype == LSNIF_FP32) return launch_lat(a, ob.F, g, s);
-            if (ob.mlp_dtype == LSNIF_FP16) return launch_mma_small_f16(a, ob.feat_dtype, kbm, g, s);
-            if (ob.mlp_dtype == LSNIF_BF16) return launch_mma_small_bf16(a, ob.feat_dtype, kbm, g, s);
-            return launch_mma_small_fp8(a, ob.feat_dtype, kbm, g, s);
-        }
-        if (ob.mlp_dtype == LSNIF_FP32) return launch_f32(a, ob.feat_dtype, ob.F, false, g, s);
-        if (ob.mlp_dtype == LSNIF_FP16) return launch_mma_f16(a, ob.feat_dtype, ob.F, kbm, false, g, s);
-        if (ob.mlp_dtype == LSNIF_BF16) return launch_mma_bf16(a, ob.feat_dtype, ob.F, kbm, false, g, s);
-        return launch_mma_fp8(a, ob.feat_dtype, ob.F, kbm, false, g, s);
+        const int L = ob.geom.L;
+        if (ob.mlp_dtype == LSNIF_FP32) return launch_query_f32(a, ob.feat_dtype, ob.F, L, false, g, s);
+        if (ob.mlp_dtype == LSNIF_FP16) return launch_query_f16(a, ob.feat_dtype, ob.F, L, false, g, s);
+        if (ob.mlp_dtype == LSNIF_BF16) return launch_query_bf16(a, ob.feat_dtype, ob.F, L, false, g, s);
+        return launch_query_fp8(a, ob.feat_dtype, ob.F, L, false, g, s);
     };
     const uint32_t k = dbg ? 1u : (chunks > 0 ? (uint32_t)chunks : ob.walk_chunks);
     lsnif_status st = walk_then_query(ctx, A, false, ob.geom.recheck != 0, (uint32_t)ob.geom.V, grid, k, s, ev[2], query);
@@ -838,9 +793,7 @@ lsnif_status pairs_setup(lsnif_ctx *ctx, PairsSetup &ps)
 {
     if (ctx->objects.empty()) return fail(LSNIF_E_NOTFOUND, "no objects built");
     ps.first = &ctx->objects.begin()->second;
-    ps.kbm = 1;
     ps.maxH = 2;
-    ps.hot_max = 0;
     ps.recheck = false;
     ps.walk_chunks = 1;
     ps.pair_bits = 1;
@@ -848,14 +801,12 @@ lsnif_status pairs_setup(lsnif_ctx *ctx, PairsSetup &ps)
         if (!same_class(kv.second, *ps.first))
             return fail(LSNIF_E_INVALID, "pair queries need every object of the context in one kernel class "
                                          "(feature type, MLP type, F, width)");
-        ps.kbm = std::max(ps.kbm, kv.second.mlp.kb_point);
         ps.maxH = std::max(ps.maxH, kv.second.geom.H);
+        ps.max_L = std::max(ps.max_L, kv.second.geom.L);
         ps.max_V = std::max(ps.max_V, (uint32_t)kv.second.geom.V);
-        ps.hot_max = std::max(ps.hot_max, kv.second.geom.hot_bytes);
         ps.recheck = ps.recheck || kv.second.geom.recheck;
         ps.walk_chunks = std::max(ps.walk_chunks, kv.second.walk_chunks);
         ps.pair_bits = std::max(ps.pair_bits, kv.second.geom.pair_bits);
-        ps.persistent = std::max(ps.persistent, kv.second.persistent);
     }
     lsnif_status st = upload_table(ctx, ps.n_objs);
     if (st) return st;
@@ -928,7 +879,6 @@ lsnif_status enqueue_pairs(lsnif_ctx *ctx, const PairsSetup &ps, const lsnif_ray
     if (n_pairs) {
         QueryArgs A{};
         A.g.H = ps.maxH;
-        A.hot_lds = ps.hot_max;   // every object's hot levels fit
         A.width = (uint32_t)first.width;   // one kernel class: every object has this width
         A.rays = P.rays;
         A.n = n_slots;
@@ -942,16 +892,14 @@ lsnif_status enqueue_pairs(lsnif_ctx *ctx, const PairsSetup &ps, const lsnif_ray
         A.pr.res = P.res;
         A.nvox = nvox;
         A.lists = lists;
-        A.queue = reinterpret_cast<unsigned long long *>(w + list_ws_bytes(n_slots, (uint32_t)ps.maxH >> 1));
-        A.persistent = ps.persistent;
-        const int kbm = ps.kbm;
         const uint32_t k = chunks > 0 ? (uint32_t)chunks : ps.walk_chunks;
         lsnif_status st = walk_then_query(ctx, A, true, ps.recheck, ps.max_V, n_tiles, k, s, ev[2],
                                           [&](const QueryArgs &a, uint32_t g) -> hipError_t {
-            if (first.mlp_dtype == LSNIF_FP32) return launch_f32(a, first.feat_dtype, first.F, true, g, s);
-            if (first.mlp_dtype == LSNIF_FP16) return launch_mma_f16(a, first.feat_dtype, first.F, kbm, true, g, s);
-            if (first.mlp_dtype == LSNIF_BF16) return launch_mma_bf16(a, first.feat_dtype, first.F, kbm, true, g, s);
-            return launch_mma_fp8(a, first.feat_dtype, first.F, kbm, true, g, s);
+            const int L = ps.max_L;
+            if (first.mlp_dtype == LSNIF_FP32) return launch_query_f32(a, first.feat_dtype, first.F, L, true, g, s);
+            if (first.mlp_dtype == LSNIF_FP16) return launch_query_f16(a, first.feat_dtype, first.F, L, true, g, s);
+            if (first.mlp_dtype == LSNIF_BF16) return launch_query_bf16(a, first.feat_dtype, first.F, L, true, g, s);
+            return launch_query_fp8(a, first.feat_dtype, first.F, L, true, g, s);
         });
         if (st) return st;
     }

@@ -36,10 +36,9 @@ struct Object {
     Mlp mlp{};
     void *d_occ = nullptr, *d_tab = nullptr, *d_w = nullptr;   // d_occ: brick masks, then brick bits
     int feat_dtype = 0, mlp_dtype = 0, F = 0, width = 0;
-    uint32_t esz = 0;             // bytes of one table entry on the device
-    uint32_t hot_budget = kHotLdsBudget;   // LDS budget the hot levels were planned for
+    uint32_t hot_budget = 0;      // the tuning's hot_lds_bytes and persistent: kept and reported, nothing reads them
     uint32_t walk_chunks = kWalkChunks;    // tile ranges of a query whose walk runs ahead
-    uint32_t persistent = 0;               // query kernel as a persistent grid (width 64)
+    uint32_t persistent = 0;
     uint64_t bytes = 0;
 };
 
@@ -68,8 +67,6 @@ void destroy_server(lsnif_ctx *ctx);   // stops a running serving loop
 
 // Batches below this size are processed in the order given (no coherence sort).
 constexpr uint32_t kSortMin = 8192;
-// FP32 batches of at most this many rays run one wave per ray (k_query_lat).
-constexpr uint32_t kSmallBatchRays = 8192;
 
 // Workspace bytes of one query of n rays, and of one pair query; cap is the
 // longest voxel list (H / 2, the largest over the objects for pairs).
@@ -123,13 +120,12 @@ namespace lsnif {
 // Class of the objects a pair query can reach, uploaded object table included.
 struct PairsSetup {
     const Object *first = nullptr;
-    int kbm = 1, maxH = 2;
+    int maxH = 2;
+    int max_L = 1;          // most levels of the objects
     uint32_t max_V = 1;     // largest voxel grid of the objects
-    uint32_t hot_max = 0;   // largest hot-level LDS footprint of the objects
     bool recheck = false;   // some object re-decides grazing voxels in float64
     uint32_t walk_chunks = 1;   // largest walk_chunks of the objects
     uint32_t pair_bits = 1;     // finest pair grouping of the objects
-    uint32_t persistent = 0;    // some object asks for the persistent query kernel
     uint32_t n_objs = 0;
 };
 lsnif_status pairs_setup(lsnif_ctx *ctx, PairsSetup &ps);
@@ -137,8 +133,6 @@ lsnif_status pairs_setup(lsnif_ctx *ctx, PairsSetup &ps);
 lsnif_status upload_table(lsnif_ctx *ctx, uint32_t &n_objs);
 // Grow a device workspace to `need` bytes (frees the old one, which waits for its users).
 lsnif_status grow_workspace(void *&buf, size_t &have, size_t need);
-// Choose an object's hot levels for an LDS budget (bytes).
-void plan_hot_levels(Geom &g, uint32_t esz, uint32_t budget);
 // Object `object_id` of ctx and the checks every single-object query makes.
 lsnif_status check_query(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray *d_rays, uint32_t n, lsnif_hit *d_out,
                          const Object *&ob);
@@ -150,7 +144,7 @@ lsnif_status check_query(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray *d_
 lsnif_status enqueue_query(lsnif_ctx *ctx, const Object &ob, const lsnif_ray *d_rays, uint32_t n, lsnif_hit *d_out,
                            const lsnif_debug_bufs *dbg, hipStream_t s, void *ws, int chunks = 0,
                            float *gather_sums = nullptr, bool timed = true);
-// Launch parameters: range checks, and setting them on an object (re-plans its hot levels).
+// Launch parameters: range checks, and setting them on an object.
 lsnif_status check_tuning(const lsnif_tuning *t);
 void apply_tuning(lsnif_ctx *ctx, Object &ob, const lsnif_tuning &t);
 lsnif_tuning object_tuning(const Object &ob);

@@ -1,12 +1,6 @@
-// Query kernels for gfx950.
-//
-//  k_query_f32   one ray per lane; fused walk, encoding, float32 MLP on the
-//                vector ALU (weights are wave-uniform scalar operands), decode.
-//  k_query_mma   one ray per lane, 64 rays per wave; the same walk and
-//                encoding, then every MLP layer on the matrix cores
-//                (v_mfma_f32_32x32x16_{f16,bf16}, float32 accumulation).
-//  k_debug       one ray per lane; writes every intermediate of the walk and
-//                the grid lookups for bit-exact checks.
+// Types and device functions the kernels share (gfx950): kernel arguments, the
+// hash-grid encoding, matrix-core operand types, decode, and the walk and
+// gather-ceiling kernels.
 #pragma once
 #pragma clang fp contract(off)
 
@@ -86,13 +80,9 @@ struct QueryArgs {
     uint32_t *lists;          // voxel lists by slot: entry j of slot i at lists[j n + i]
     uint8_t *nvox;            // listed voxels of each slot
     uint32_t tile0;           // first tile of the launch (a launch may cover a range of the tiles)
-    uint32_t n_tiles;         // tiles of the launch (persistent kernels: the range they share out)
-    unsigned long long *queue;   // persistent kernels: 8 tile-queue counters, zero at launch
-    uint32_t persistent;      // run the query kernel as a persistent grid (width-64 matrix-core kernels)
     uint32_t width;           // hidden width of the launch's objects (64 or 128), picks the kernel
     Dbg dbg;
     PairArgs pr;
-    uint32_t hot_lds;         // dynamic LDS bytes after the voxel lists for hot levels
 };
 
 // Order-preserving map of a float to 32 unsigned bits.
@@ -206,15 +196,12 @@ __device__ __forceinline__ void level_cell_mm(const Geom &g, int l, const float 
 // beyond L give zeros.  All slots are formed first and all gathers issued
 // before any is consumed.  On a level aligned with the voxel faces the
 // crossing-axis weight is exactly 0 or 1, and the 4 zero-weight corners do
-// not touch their own entries (the LDS variant re-reads the 4 face corners,
-// the other reads the level's first entry).
-template <typename TF, int F, int NL, bool HOT>
-__device__ __forceinline__ void encode_levels(const Geom &g, const TF *__restrict__ tab, const uint32_t *hot, int l0,
-                                              const float p[3], int face, float out[NL][F])
+// not touch their own entries (they read the level's first entry).
+template <typename TF, int F, int NL>
+__device__ __forceinline__ void encode_levels(const Geom &g, const TF *__restrict__ tab, int l0, const float p[3],
+                                              int face, float out[NL][F])
 {
     const char *base[NL];
-    bool in_lds[NL];
-    uint32_t hoff[NL];
     uint32_t off[NL][8];
     float wx[NL][2], wy[NL][2], wz[NL][2];
     constexpr uint32_t esz = F * sizeof(TF);
@@ -223,69 +210,44 @@ __device__ __forceinline__ void encode_levels(const Geom &g, const TF *__restric
         const int l = l0 + lv < g.L ? l0 + lv : g.L - 1;
         uint32_t i[3];
         float wt[3];
-        if constexpr (HOT) {
-            // the LDS variant keeps the branch-free form: with the wave-uniform branches
-            // below, the compiler merges the LDS and HBM gathers into flat loads
-            level_cell(g, l, p, i, wt);
-            const uint32_t my = g.my[l], mz = g.mz[l];
-            uint32_t t[3][2] = {{i[0], i[0] + 1u}, {i[1] * my, i[1] * my + my}, {i[2] * mz, i[2] * mz + mz}};
-            const bool al = (g.aligned_mask >> l) & 1u;
-            const float wf = face == 0 ? wt[0] : (face == 1 ? wt[1] : wt[2]);
+        level_cell_mm(g, l, p, i, wt);
+        // With a power-of-two entry size the byte offset is formed directly: scaling
+        // x, y my and z mz by esz commutes with the sum and, as a shift, with the xor
+        // and the mask.
+        constexpr uint32_t sh = esz == 4 ? 2u : (esz == 8 ? 3u : (esz == 16 ? 4u : 0u));
+        constexpr bool scaled = sh != 0u;
+        const uint32_t my = g.my[l] << sh, mz = g.mz[l] << sh;
+        const uint32_t x0 = i[0] << sh;
+        uint32_t t[3][2] = {{x0, x0 + (1u << sh)}, {i[1] * my, i[1] * my + my}, {i[2] * mz, i[2] * mz + mz}};
+        // vertex slot: x + y + z on a directly indexed level, (x ^ y ^ z) & (T - 1) on a
+        // hashed one (y, z already times their multipliers); the level kind is wave-uniform
+        constexpr uint32_t m = scaled ? 1u : esz;
+        if ((g.dense_mask >> l) & 1u) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const bool col = al && a == face;
-                const uint32_t sel = wf != 0.0f ? t[a][1] : t[a][0];
-                t[a][0] = col ? sel : t[a][0];
-                t[a][1] = col ? sel : t[a][1];
-            }
-            const uint32_t dm = g.dmask[l], hm = g.hmask[l];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const uint32_t x = t[0][c & 1], y = t[1][(c >> 1) & 1], z = t[2][c >> 2];
-                off[lv][c] = (((x + y + z) & dm) | ((x ^ y ^ z) & hm)) * esz;
-            }
+            for (int c = 0; c < 8; ++c)
+                off[lv][c] = (t[0][c & 1] + t[1][(c >> 1) & 1] + t[2][c >> 2]) * m;
         } else {
-            level_cell_mm(g, l, p, i, wt);
-            // With a power-of-two entry size the byte offset is formed directly: scaling
-            // x, y my and z mz by esz commutes with the sum and, as a shift, with the xor
-            // and the mask.
-            constexpr uint32_t sh = esz == 4 ? 2u : (esz == 8 ? 3u : (esz == 16 ? 4u : 0u));
-            constexpr bool scaled = sh != 0u;
-            const uint32_t my = g.my[l] << sh, mz = g.mz[l] << sh;
-            const uint32_t x0 = i[0] << sh;
-            uint32_t t[3][2] = {{x0, x0 + (1u << sh)}, {i[1] * my, i[1] * my + my}, {i[2] * mz, i[2] * mz + mz}};
-            // vertex slot: x + y + z on a directly indexed level, (x ^ y ^ z) & (T - 1) on a
-            // hashed one (y, z already times their multipliers); the level kind is wave-uniform
-            constexpr uint32_t m = scaled ? 1u : esz;
-            if ((g.dense_mask >> l) & 1u) {
+            const uint32_t hm = g.hmask[l] << sh;
 #pragma unroll
-                for (int c = 0; c < 8; ++c)
-                    off[lv][c] = (t[0][c & 1] + t[1][(c >> 1) & 1] + t[2][c >> 2]) * m;
-            } else {
-                const uint32_t hm = g.hmask[l] << sh;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t yz = t[1][q & 1] ^ t[2][q >> 1];
-                    off[lv][2 * q] = ((t[0][0] ^ yz) & hm) * m;
-                    off[lv][2 * q + 1] = ((t[0][1] ^ yz) & hm) * m;
-                }
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t yz = t[1][q & 1] ^ t[2][q >> 1];
+                off[lv][2 * q] = ((t[0][0] ^ yz) & hm) * m;
+                off[lv][2 * q + 1] = ((t[0][1] ^ yz) & hm) * m;
             }
-            if ((g.aligned_mask >> l) & 1u) {
-                // On a face-aligned level the crossing axis' weight is exactly 0 or 1, so the 4
-                // corners on the other side weigh 0.  They read the level's first entry: one
-                // line for every lane, where their own slots would cost the addresser a line
-                // per lane.  Weight 0 times a finite entry adds nothing (the sum is never -0).
-                const float wf = face == 0 ? wt[0] : (face == 1 ? wt[1] : wt[2]);
-                const uint32_t fb = 1u << face, keep = wf != 0.0f ? fb : 0u;
+        }
+        if ((g.aligned_mask >> l) & 1u) {
+            // On a face-aligned level the crossing axis' weight is exactly 0 or 1, so the 4
+            // corners on the other side weigh 0.  They read the level's first entry: one
+            // line for every lane, where their own slots would cost the addresser a line
+            // per lane.  Weight 0 times a finite entry adds nothing (the sum is never -0).
+            const float wf = face == 0 ? wt[0] : (face == 1 ? wt[1] : wt[2]);
+            const uint32_t fb = 1u << face, keep = wf != 0.0f ? fb : 0u;
 #pragma unroll
-                for (int c = 0; c < 8; ++c) off[lv][c] = ((uint32_t)c & fb) == keep ? off[lv][c] : 0u;
-            }
+            for (int c = 0; c < 8; ++c) off[lv][c] = ((uint32_t)c & fb) == keep ? off[lv][c] : 0u;
         }
         wx[lv][0] = 1.0f - wt[0]; wx[lv][1] = wt[0];
         wy[lv][0] = 1.0f - wt[1]; wy[lv][1] = wt[1];
         wz[lv][0] = 1.0f - wt[2]; wz[lv][1] = wt[2];
-        in_lds[lv] = HOT && ((g.hot_mask >> l) & 1u);
-        hoff[lv] = HOT ? g.hot_off[l] : 0u;
         base[lv] = reinterpret_cast<const char *>(tab + ((size_t)l << g.log2_T) * F);
     }
     Entry<TF, F> e[NL][8];
@@ -293,7 +255,7 @@ __device__ __forceinline__ void encode_levels(const Geom &g, const TF *__restric
 #pragma unroll
     for (int lv = 0; lv < NL; ++lv) {
         const int l = l0 + lv < g.L ? l0 + lv : g.L - 1;
-        const bool pairx = !HOT && F * sizeof(TF) == 4 && ((g.dense_mask & ~g.aligned_mask) >> l) & 1u;
+        const bool pairx = F * sizeof(TF) == 4 && ((g.dense_mask & ~g.aligned_mask) >> l) & 1u;
         if (pairx) {
             // directly indexed level: the two x-vertices of an edge are adjacent entries
 #pragma unroll
@@ -304,11 +266,7 @@ __device__ __forceinline__ void encode_levels(const Geom &g, const TF *__restric
             }
         } else {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                // a hot level is read from its LDS copy (the pointer stays in the LDS address space)
-                if (HOT && in_lds[lv]) e[lv][c].load(reinterpret_cast<const char *>(hot) + hoff[lv], off[lv][c]);
-                else e[lv][c].load(base[lv], off[lv][c]);
-            }
+            for (int c = 0; c < 8; ++c) e[lv][c].load(base[lv], off[lv][c]);
         }
     }
     // keep every gather of the batch in flight before the first is consumed
@@ -334,28 +292,6 @@ __device__ __forceinline__ void encode_levels(const Geom &g, const TF *__restric
         if (l0 + lv >= g.L) {
 #pragma unroll
             for (int f = 0; f < F; ++f) out[lv][f] = 0.0f;
-        }
-    }
-}
-
-// Tables with 4- or 8-byte entries may keep their coarsest levels in LDS.
-template <typename TF, int F> constexpr bool hot_entries()
-{
-    return F * sizeof(TF) == 4 || F * sizeof(TF) == 8;
-}
-
-// Copy the object's hot levels (the coarsest, all of whose used slots fit the
-// LDS budget) into LDS; every ray of the block reads them.  Visible after the
-// block's next barrier.
-template <typename TF, int F>
-__device__ __forceinline__ void stage_hot_levels(const Geom &g, const TF *__restrict__ tab, uint32_t *hot)
-{
-    if constexpr (hot_entries<TF, F>()) {
-        for (int l = 0; l < g.L; ++l) {
-            if (!((g.hot_mask >> l) & 1u)) continue;
-            const uint4 *src = reinterpret_cast<const uint4 *>(tab + ((size_t)l << g.log2_T) * F);
-            uint4 *dst = reinterpret_cast<uint4 *>(hot) + (g.hot_off[l] >> 4);
-            for (uint32_t i = threadIdx.x; i < (g.hot_len[l] >> 4); i += kBlock) dst[i] = src[i];
         }
     }
 }
@@ -445,9 +381,9 @@ __device__ __forceinline__ void decode_store(const QueryArgs &A, const Mlp &mm, 
 
 // ------------------------------------------------------------- shared prologue
 //
-// The walk kernel lists the voxels of slot blockIdx-tile * kBlock + threadIdx.x
-// into the workspace; the query kernels then load each slot's list into LDS
-// and order the block's rays by voxel count (most first), so that each wave
+// The walk kernels list the voxels of every slot into the workspace; the
+// gather-ceiling kernel then loads each slot's list into LDS
+// and orders the block's rays by voxel count (most first), so that each wave
 // encodes rays with similar numbers of boundary points.  After the prologue,
 // lane `tid` works on ray `src` of the block; its voxel list is at
 // s_list[j * kBlock + src] and its walk state has been reloaded from LDS.
@@ -484,47 +420,6 @@ __device__ __forceinline__ uint32_t block_tile(uint32_t tile0)
     if (b >= full) return tile0 + b;
     const uint32_t x = b & 7u, k = b >> 3;
     return tile0 + ((k / C) * 8u + x) * C + k % C;
-}
-
-// Persistent query kernels: a grid of as many blocks as fit on the chip at once,
-// each taking tiles until none are left.  The launch's n_tiles tiles are cut
-// into 8 contiguous ranges of the coherence order, range x for the blocks that
-// run on XCD x (blockIdx mod 8: the dispatcher's round robin), so each XCD's
-// L2 serves one stretch of rays (or of one object's pairs) at a time.  A
-// block takes the next tile from the head of its own range; once that range
-// is empty it takes tiles from the tails of the other ranges.  Each range's
-// counter packs the head claims (low 32 bits) and the tail claims (high 32
-// bits) into one 64-bit word, so one atomic add both claims and sees the
-// other side: a head claim h is valid iff h + s < len, a tail claim iff
-// len - 1 - s >= h, for the (h, s) it read.  Every tile is claimed exactly
-// once, every claim fails once the range is used up, and each block leaves
-// when all eight ranges are: the grid always drains.
-constexpr uint32_t kNoTile = 0xffffffffu;
-
-__device__ __forceinline__ uint32_t queue_take(const QueryArgs &A, uint32_t x)
-{
-    for (uint32_t q = 0; q < 8u; ++q) {
-        const uint32_t v = (x + q) & 7u;
-        const uint32_t lo = (uint32_t)((uint64_t)A.n_tiles * v / 8u);
-        const uint32_t len = (uint32_t)((uint64_t)A.n_tiles * (v + 1u) / 8u) - lo;
-        unsigned long long *c = A.queue + v;
-        const unsigned long long seen = __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((uint64_t)(uint32_t)seen + (seen >> 32) >= len) continue;   // used up (the atomic decides)
-        const unsigned long long old = atomicAdd(c, q == 0 ? 1ull : (1ull << 32));
-        const uint32_t h = (uint32_t)old, s = (uint32_t)(old >> 32);
-        if ((uint64_t)h + s < len) return A.tile0 + lo + (q == 0 ? h : len - 1u - s);
-    }
-    return kNoTile;
-}
-
-// The block's next tile (kNoTile: none left), the same value for every thread.
-// The trailing barrier also ends the block's use of LDS for the previous tile.
-__device__ __forceinline__ uint32_t next_tile(const QueryArgs &A, uint32_t &s_tile)
-{
-    __syncthreads();
-    if (threadIdx.x == 0) s_tile = queue_take(A, blockIdx.x & 7u);
-    __syncthreads();
-    return __builtin_amdgcn_readfirstlane(s_tile);
 }
 
 template <bool PAIRS>
@@ -650,11 +545,6 @@ __device__ __forceinline__ void walk_and_sort(const QueryArgs &A, const Geom &g,
     L.live = PAIRS ? L.pair != 0xffffffffu : tile * kBlock + src < A.n;
 }
 
-// ---------------------------------------------------------------- float32 path
-//
-// Weights: layer k transposed to [in][out_pad] float32 (out_pad = WIDTH for
-// hidden layers, kMaxOut for the head) so the outputs fed by one input are
-// contiguous and every lane reads the same address.
 // Object of this block's tile: one value for the whole block, read through the
 // scalar path so that everything derived from it (tables, weights) stays uniform.
 __device__ __forceinline__ int tile_object(const PairArgs &P, uint32_t tile)
@@ -670,147 +560,16 @@ typedef const __attribute__((address_space(4))) ObjDev cObjDev;
 typedef const ObjDev cObjDev;
 #endif
 
-// A float in the constant address space (read-only during a launch; scalar loads).
-typedef const __attribute__((address_space(4))) float cfloat;
-
-template <typename TF, int F, int WIDTH, bool PAIRS, bool HOT>
-__device__ __forceinline__ void query_f32_body(const QueryArgs &A, const Geom &g, const Mlp &mm,
-                                               const TF *__restrict__ tab, uint32_t *s_list, Shared &S,
-                                               uint32_t tile)
-{
-    constexpr int NL = 4;
-    Lane ln;
-    uint32_t *hot = s_list + (A.g.H >> 1) * kBlock;   // after the voxel lists (sized for the launch)
-    if constexpr (HOT) stage_hot_levels<TF, F>(g, tab, hot);
-    walk_and_sort<PAIRS>(A, g, S, s_list, ln, tile);
-    const uint32_t src = ln.src, r = ln.r;
-    const bool live = ln.live;
-    const VRay &w = ln.w;
-    const int count = 2 * ln.nvox;
-    const int wmax = __builtin_amdgcn_readfirstlane(wave_max(count));
-    // The weights are read-only for the whole launch and every lane of a wave reads the same
-    // one: through the constant address space the loads are scalar and the FMAs take them
-    // from scalar registers.
-    const cfloat *Wf = (const cfloat *)(mm.W);
-    const int LF = g.L * F;
-
-    float acc[WIDTH];
-#pragma unroll
-    for (int j = 0; j < WIDTH; ++j) acc[j] = 0.0f;
-    float amax = 0.0f;        // largest |input| of the current layer (calibration)
-    for (int h = 0; h < wmax; ++h) {
-        if (h < count) {
-            float p[3];
-            const int face = boundary_point(w, s_list[(h >> 1) * kBlock + src], h & 1, p);
-            for (int l0 = 0; l0 < g.L; l0 += NL) {
-                float e[NL][F];
-                encode_levels<TF, F, NL, HOT>(g, tab, hot, l0, p, face, e);
-#pragma unroll
-                for (int lv = 0; lv < NL; ++lv) {
-                    const int l = l0 + lv;
-                    if (l < g.L) {
-#pragma unroll
-                        for (int f = 0; f < F; ++f) amax = fmax2(amax, __builtin_fabsf(e[lv][f]));
-                        if (A.dbg.enc) {
-#pragma unroll
-                            for (int f = 0; f < F; ++f)
-                                A.dbg.enc[(size_t)r * g.H * LF + h * LF + l * F + f] = e[lv][f];
-                        }
-                        const cfloat *Wk = Wf + mm.off[0] + (size_t)(h * LF + l * F) * WIDTH;
-#pragma unroll
-                        for (int f = 0; f < F; ++f)
-#pragma unroll
-                            for (int j = 0; j < WIDTH; ++j) acc[j] = __builtin_fmaf(Wk[f * WIDTH + j], e[lv][f], acc[j]);
-                    }
-                }
-            }
-        }
-    }
-    float o[kMaxOut];
-#pragma unroll
-    for (int k = 0; k < kMaxOut; ++k) o[k] = 0.0f;
-    if (A.dbg.act_amax) fold_max(A.dbg.act_amax + 0, amax);
-    if (wmax > 0) {
-        for (int k = 1; k < mm.n_hidden; ++k) {
-            float nxt[WIDTH];
-#pragma unroll
-            for (int j = 0; j < WIDTH; ++j) nxt[j] = 0.0f;
-            const cfloat *Wk = Wf + mm.off[k];
-            amax = 0.0f;
-#pragma unroll
-            for (int i = 0; i < WIDTH; ++i) {
-                const float x = act_f(acc[i], mm.act, mm.slope);
-                amax = fmax2(amax, __builtin_fabsf(x));
-#pragma unroll
-                for (int j = 0; j < WIDTH; ++j) nxt[j] = __builtin_fmaf(Wk[i * WIDTH + j], x, nxt[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < WIDTH; ++j) acc[j] = nxt[j];
-            if (A.dbg.act_amax) fold_max(A.dbg.act_amax + k, amax);
-        }
-        const cfloat *Wo = Wf + mm.off[mm.n_hidden];
-        amax = 0.0f;
-#pragma unroll
-        for (int i = 0; i < WIDTH; ++i) {
-            const float x = act_f(acc[i], mm.act, mm.slope);
-            amax = fmax2(amax, __builtin_fabsf(x));
-#pragma unroll
-            for (int j = 0; j < kMaxOut; ++j) o[j] = __builtin_fmaf(Wo[i * kMaxOut + j], x, o[j]);
-        }
-        if (A.dbg.act_amax) fold_max(A.dbg.act_amax + mm.n_hidden, amax);
-    }
-    if (!live) return;
-    if (A.dbg.count) A.dbg.count[r] = w.valid ? count : -1;
-    if (A.dbg.tatb) {
-        A.dbg.tatb[2 * r] = w.ta;
-        A.dbg.tatb[2 * r + 1] = w.tb;
-    }
-    if (A.dbg.out) {
-#pragma unroll
-        for (int k = 0; k < kMaxOut; ++k)
-            if (k < mm.out_dim) A.dbg.out[(size_t)r * mm.out_dim + k] = count > 0 ? o[k] : 0.0f;
-    }
-    decode_store<PAIRS>(A, mm, r, ln.pair, w, count, o);
-}
-
-template <typename TF, int F, int WIDTH, bool PAIRS, bool HOT>
-__device__ __forceinline__ void query_f32_tile(const QueryArgs &A, uint32_t *s_list, Shared &S, uint32_t tile)
-{
-    if constexpr (PAIRS) {
-        const int o = tile_object(A.pr, tile);
-        if (o < 0) return;
-        const cObjDev &O = ((const cObjDev *)A.pr.objs)[o];
-        query_f32_body<TF, F, WIDTH, true, HOT>(A, O.g, O.m, (const TF *)O.tables, s_list, S, tile);
-    } else {
-        query_f32_body<TF, F, WIDTH, false, HOT>(A, A.g, A.m, reinterpret_cast<const TF *>(A.tables), s_list, S,
-                                                 tile);
-    }
-}
-
-template <typename TF, int F, int WIDTH, bool PAIRS, bool HOT>
-__global__ __launch_bounds__(kBlock) void k_query_f32(QueryArgs A)
-{
-    extern __shared__ uint32_t s_list[];
-    __shared__ Shared S;
-    query_f32_tile<TF, F, WIDTH, PAIRS, HOT>(A, s_list, S, block_tile(A.tile0));
-}
-
-
-// ------------------------------------------------------------ matrix-core path
+// ------------------------------------------------------------ matrix-core types
 //
 // Layer k computes D = W_k * X with the weights as the A operand (M = output
 // units, 32 per block) and the activations as the B operand (N = rays, 32 per
-// block, two blocks per wave), v_mfma_f32_32x32x16.  Operand layout per lane
-// l (i = l % 32, half q = l / 32): A holds W[i][8q .. 8q+7] of the K block,
-// B holds X[8q .. 8q+7][i], and the 16 accumulators hold
-// D[8(r/4) + 4q + r%4][i], r = 0..15.
-//
-// Layer 1 input: lane l encodes its own ray; per 16-wide K block it holds the
-// ray's features k0..7 and k8..15, and one permlane32 swap turns these into
-// the B operands of ray blocks 0-31 and 32-63.  Hidden layers take the
-// accumulators as they lie: K slot 8q + e of 16-block s of output block m
-// stands for unit 32m + 16s + (e < 4 ? 4q + e : 8 + 4q + e - 4); the host
-// packs the weights of later layers in that order.
+// block), v_mfma_f32_32x32x16.  Operand layout per lane l (i = l % 32, half
+// q = l / 32): A holds W[i][8q .. 8q+7] of the K block, B holds X[8q .. 8q+7][i],
+// and the 16 accumulators hold D[8(r/4) + 4q + r%4][i], r = 0..15.  Hidden
+// layers take the accumulators as they lie: K slot 8q + e of 16-block s of
+// output block m stands for unit 32m + 16s + (e < 4 ? 4q + e : 8 + 4q + e - 4);
+// the host packs the weights of later layers in that order.
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 b8_t __attribute__((ext_vector_type(8)));
 typedef float f16_t __attribute__((ext_vector_type(16)));
@@ -920,628 +679,6 @@ template <int DW> __device__ __forceinline__ void load_frag(const uint32_t *p, u
     }
 }
 
-// Exchange the upper half-wave of x with the lower half-wave of y.
-__device__ __forceinline__ void swap32(uint32_t &x, uint32_t &y)
-{
-    auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-    x = r[0];
-    y = r[1];
-}
-
-template <typename TF, typename TM, int F, int WIDTH, int KBM, bool PAIRS, bool HOT>
-__device__ __forceinline__ void query_mma_body(const QueryArgs &A, const Geom &g, const Mlp &mm,
-                                               const TF *__restrict__ tab, uint32_t *s_list, Shared &S,
-                                               uint32_t tile)
-{
-    typedef typename MmaT<TM>::vec vec_t;
-    constexpr int DW = MmaT<TM>::DW;
-    constexpr int FP = F == 3 ? 4 : F;        // features per level, padded to divide 16
-    constexpr int MB = WIDTH / 32;            // output blocks of a hidden layer
-    constexpr int LPB = 16 / FP;              // levels per K block
-    constexpr int NL = (F * sizeof(TF) <= 4 && LPB >= 8) ? 8 : (LPB < 4 ? LPB : 4);   // levels per gather batch
-    Lane ln;
-    uint32_t *hot = s_list + (A.g.H >> 1) * kBlock;   // after the voxel lists (sized for the launch)
-    if constexpr (HOT) stage_hot_levels<TF, F>(g, tab, hot);
-    walk_and_sort<PAIRS>(A, g, S, s_list, ln, tile);
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t src = ln.src, r = ln.r;
-    const bool live = ln.live;
-    const VRay &w = ln.w;
-    const int count = 2 * ln.nvox;
-    const int wmax = __builtin_amdgcn_readfirstlane(wave_max(count));
-    const uint32_t *__restrict__ Wv = reinterpret_cast<const uint32_t *>(mm.W);
-    const int KB = mm.kb_point;
-
-    f16_t acc[MB][2];
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[m][nb][e] = 0.0f;
-
-    // The entry point of a voxel equals the exit point of the voxel before it
-    // when the two share a face (about 30 % of points on c2); such a point
-    // reuses the previous point's features, so its lane issues no gathers.
-    uint32_t plo[KBM][DW], phi[KBM][DW];
-#pragma unroll
-    for (int kb = 0; kb < KBM; ++kb)
-#pragma unroll
-        for (int q = 0; q < DW; ++q) plo[kb][q] = phi[kb][q] = 0u;
-    uint32_t pp[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu};
-    int pface = -1;
-    for (int h = 0; h < wmax; ++h) {
-        float p[3] = {0.0f, 0.0f, 0.0f};
-        int face = 0;
-        const bool has = h < count;
-        if (has) face = boundary_point(w, s_list[(h >> 1) * kBlock + src], h & 1, p);
-        const bool dup = has && (h & 1) == 0 && face == pface && __float_as_uint(p[0]) == pp[0] &&
-                         __float_as_uint(p[1]) == pp[1] && __float_as_uint(p[2]) == pp[2];
-        const bool fresh = has && !dup;
-#pragma unroll
-        for (int kb = 0; kb < KBM; ++kb) {
-            if (kb >= KB) break;
-            // this K block's layer-1 weight fragments, requested ahead of the gathers so that
-            // their latency overlaps the gathers' rather than following them
-            uint32_t wd[MB][DW];
-            const uint32_t *Wk = Wv + mm.woff[0] + ((size_t)((h * KB + kb) * MB) * 64 + lane) * DW;
-#pragma unroll
-            for (int m = 0; m < MB; ++m) load_frag<DW>(Wk + (size_t)m * 64 * DW, wd[m]);
-            uint32_t lo[DW], hi[DW];
-            if (fresh) {
-                float e[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) e[q] = 0.0f;
-#pragma unroll
-                for (int c0 = 0; c0 < LPB; c0 += NL) {
-                    float v[NL][F];
-                    encode_levels<TF, F, NL, HOT>(g, tab, hot, kb * LPB + c0, p, face, v);
-#pragma unroll
-                    for (int lv = 0; lv < NL; ++lv)
-#pragma unroll
-                        for (int f = 0; f < F; ++f) e[(c0 + lv) * FP + f] = v[lv][f];
-                }
-                pack8<TM>(e, mm.qs[0], lo);
-                pack8<TM>(e + 8, mm.qs[0], hi);
-            } else {
-#pragma unroll
-                for (int q = 0; q < DW; ++q) {
-                    lo[q] = dup ? plo[kb][q] : 0u;
-                    hi[q] = dup ? phi[kb][q] : 0u;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < DW; ++q) {
-                plo[kb][q] = lo[q];
-                phi[kb][q] = hi[q];
-            }
-            if (A.dbg.enc && live && has) {
-                // K slot k holds feature k % FP of level k / FP; the buffer is [H][L][F]
-                const int LF = g.L * F;
-                for (int q = 0; q < 16; ++q) {
-                    const int k = kb * 16 + q, l = k / FP, f = k % FP;
-                    if (l < g.L && f < F) {
-                        const float v = q < 8 ? unpack8<TM>(lo, q) : unpack8<TM>(hi, q - 8);
-                        A.dbg.enc[(size_t)r * g.H * LF + h * LF + l * F + f] = MmaT<TM>::scaled ? v / mm.qs[0] : v;
-                    }
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < DW; ++q) swap32(lo[q], hi[q]);
-            const vec_t b0 = as_vec<vec_t, DW>(lo), b1 = as_vec<vec_t, DW>(hi);
-#pragma unroll
-            for (int m = 0; m < MB; ++m) {
-                const vec_t a = as_vec<vec_t, DW>(wd[m]);
-                acc[m][0] = MmaT<TM>::mma(a, b0, acc[m][0]);
-                acc[m][1] = MmaT<TM>::mma(a, b1, acc[m][1]);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < 3; ++b) pp[b] = __float_as_uint(p[b]);
-        pface = has ? face : -1;
-    }
-
-    // hidden layers 2..n_hidden, then the head
-    float o[kMaxOut];
-#pragma unroll
-    for (int k = 0; k < kMaxOut; ++k) o[k] = 0.0f;
-    if (wmax > 0) {
-        for (int k = 1; k <= mm.n_hidden; ++k) {
-            const bool head = k == mm.n_hidden;
-            // activations -> B operands: 16-block s of output block m holds the
-            // outputs lying in accumulator registers 8s .. 8s+7
-            const float dqi = mm.dq[k - 1], qsi = mm.qs[k];
-            const int MO = head ? 1 : MB;
-            const uint32_t *Wk = Wv + mm.woff[k] + (size_t)lane * DW;
-            // width 64: the whole layer's weight fragments requested before the activations are
-            // converted, so that their latency overlaps that work
-            constexpr int PF = MB == 2 ? MB : 1;   // output blocks prefetched
-            uint32_t wpf[PF][MB][2][DW];
-#pragma unroll
-            for (int mo = 0; mo < PF; ++mo)
-                if (mo < MO)
-#pragma unroll
-                    for (int m = 0; m < MB; ++m)
-#pragma unroll
-                        for (int s = 0; s < 2; ++s)
-                            load_frag<DW>(Wk + (size_t)((mo * MB + m) * 2 + s) * 64 * DW, wpf[mo][m][s]);
-            asm volatile("" ::: "memory");   // keep the requests ahead of the conversion
-            uint32_t xb[MB][2][2][DW];
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                    for (int s = 0; s < 2; ++s) {
-                        float v[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float y = MmaT<TM>::scaled ? acc[m][nb][8 * s + e] * dqi : acc[m][nb][8 * s + e];
-                            v[e] = act_f(y, mm.act, mm.slope);
-                        }
-                        pack8<TM>(v, qsi, xb[m][nb][s]);
-                    }
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[m][nb][e] = 0.0f;
-#pragma unroll
-            for (int mo = 0; mo < MB; ++mo) {
-                if (mo < MO) {
-#pragma unroll
-                    for (int m = 0; m < MB; ++m)
-#pragma unroll
-                        for (int s = 0; s < 2; ++s) {
-                            uint32_t wd[DW];
-                            if (mo < PF) {
-#pragma unroll
-                                for (int q = 0; q < DW; ++q) wd[q] = wpf[mo < PF ? mo : 0][m][s][q];
-                            } else {
-                                load_frag<DW>(Wk + (size_t)((mo * MB + m) * 2 + s) * 64 * DW, wd);
-                            }
-                            const vec_t a = as_vec<vec_t, DW>(wd);
-                            acc[mo][0] = MmaT<TM>::mma(a, as_vec<vec_t, DW>(xb[m][0][s]), acc[mo][0]);
-                            acc[mo][1] = MmaT<TM>::mma(a, as_vec<vec_t, DW>(xb[m][1][s]), acc[mo][1]);
-                        }
-                }
-            }
-        }
-        // bring each ray's outputs to its own lane: rows 8q + r in x, 8q + 4 + r in y
-        uint32_t x[8], y[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            x[e] = __float_as_uint(acc[0][0][e]);
-            y[e] = __float_as_uint(acc[0][1][e]);
-            swap32(x[e], y[e]);
-        }
-        const float dqo = MmaT<TM>::scaled ? mm.dq[mm.n_hidden] : 1.0f;
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                o[8 * q + rr] = __uint_as_float(x[4 * q + rr]) * dqo;
-                o[8 * q + 4 + rr] = __uint_as_float(y[4 * q + rr]) * dqo;
-            }
-    }
-    if (!live) return;
-    if (A.dbg.count) A.dbg.count[r] = w.valid ? count : -1;
-    if (A.dbg.tatb) {
-        A.dbg.tatb[2 * r] = w.ta;
-        A.dbg.tatb[2 * r + 1] = w.tb;
-    }
-    if (A.dbg.out) {
-#pragma unroll
-        for (int k = 0; k < kMaxOut; ++k)
-            if (k < mm.out_dim) A.dbg.out[(size_t)r * mm.out_dim + k] = count > 0 ? o[k] : 0.0f;
-    }
-    decode_store<PAIRS>(A, mm, r, ln.pair, w, count, o);
-}
-
-template <typename TF, typename TM, int F, int WIDTH, int KBM, bool PAIRS, bool HOT>
-__device__ __forceinline__ void query_mma_tile(const QueryArgs &A, uint32_t *s_list, Shared &S, uint32_t tile)
-{
-    if constexpr (PAIRS) {
-        const int o = tile_object(A.pr, tile);
-        if (o < 0) return;
-        const cObjDev &O = ((const cObjDev *)A.pr.objs)[o];
-        query_mma_body<TF, TM, F, WIDTH, KBM, true, HOT>(A, O.g, O.m, (const TF *)O.tables, s_list, S, tile);
-    } else {
-        query_mma_body<TF, TM, F, WIDTH, KBM, false, HOT>(A, A.g, A.m, reinterpret_cast<const TF *>(A.tables), s_list,
-                                                          S, tile);
-    }
-}
-
-template <typename TF, typename TM, int F, int WIDTH, int KBM, bool PAIRS, bool HOT>
-__global__ __launch_bounds__(kBlock) void k_query_mma(QueryArgs A)
-{
-    extern __shared__ uint32_t s_list[];
-    __shared__ Shared S;
-    query_mma_tile<TF, TM, F, WIDTH, KBM, PAIRS, HOT>(A, s_list, S, block_tile(A.tile0));
-}
-
-template <typename TF, typename TM, int F, int WIDTH, int KBM, bool PAIRS, bool HOT>
-__global__ __launch_bounds__(kBlock) void k_query_mma_persist(QueryArgs A)
-{
-    extern __shared__ uint32_t s_list[];
-    __shared__ Shared S;
-    __shared__ uint32_t s_tile;
-    for (;;) {
-        const uint32_t tile = next_tile(A, s_tile);
-        if (tile == kNoTile) break;
-        query_mma_tile<TF, TM, F, WIDTH, KBM, PAIRS, HOT>(A, s_list, S, tile);
-    }
-}
-
-// ------------------------------------------------------------- small batches
-//
-// One wave per ray, for batches too small to fill the chip with one ray per
-// lane (FP32 features and MLP, width 64, at most 16 levels): a point's
-// 8-corner gathers of up to 8 levels are spread over the lanes (lane 8q + c:
-// corner c of level 8 round + q), a butterfly sum over each level's 8 lanes
-// interpolates, and lane j then owns output j of every layer, taking the
-// layer's inputs one at a time from the lanes that hold them.  Cells, slots,
-// corner weights and every sum's order are those of the ray-per-lane FP32
-// kernel, so a ray's answer and debug outputs are the same bits whichever of
-// the two kernels its batch runs on.  The walk kernel's lists are read from
-// the workspace.
-constexpr int kLatWaves = 4;     // rays (one wave each) per workgroup
-constexpr int kLatMaxLF = 48;    // features per point: at most 16 levels of at most 3
-
-template <typename TF, int F>
-__device__ __forceinline__ void lat_level(const Geom &g, const TF *__restrict__ tab, int l, uint32_t c,
-                                          const float p[3], float v[F])
-{
-    const bool in = l < g.L;
-    const int lc = in ? l : g.L - 1;
-    uint32_t i[3];
-    float wt[3];
-    level_cell_mm(g, lc, p, i, wt);
-    const uint32_t x = i[0] + (c & 1u), y = (i[1] + ((c >> 1) & 1u)) * g.my[lc], z = (i[2] + (c >> 2)) * g.mz[lc];
-    const uint32_t s = ((x + y + z) & g.dmask[lc]) | ((x ^ y ^ z) & g.hmask[lc]);
-    const float wx = (c & 1u) ? wt[0] : 1.0f - wt[0];
-    const float wy = ((c >> 1) & 1u) ? wt[1] : 1.0f - wt[1];
-    const float wz = (c >> 2) ? wt[2] : 1.0f - wt[2];
-    const float wc = wx * (wy * wz);
-    Entry<TF, F> en;
-    en.load(reinterpret_cast<const char *>(tab + ((size_t)lc << g.log2_T) * F), s * (uint32_t)(F * sizeof(TF)));
-    // every lane of the level sums the 8 corners in corner order, as one fused
-    // multiply-add chain on the raw entries: the ray-per-lane kernel's sum, bit for bit
-    const int g0 = (int)((threadIdx.x & 63u) & ~7u);
-#pragma unroll
-    for (int f = 0; f < F; ++f) v[f] = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const float wk = __shfl(wc, g0 + k, 64);
-        Entry<TF, F> ek;
-#pragma unroll
-        for (int d = 0; d < Entry<TF, F>::W; ++d) ek.d[d] = (uint32_t)__shfl((int)en.d[d], g0 + k, 64);
-#pragma unroll
-        for (int f = 0; f < F; ++f) v[f] = __builtin_fmaf(wk, ek.get(f), v[f]);
-    }
-    if (!in) {
-#pragma unroll
-        for (int f = 0; f < F; ++f) v[f] = 0.0f;
-    }
-}
-
-// The lane's corner of lat_level without the sum: corner c of level l (levels at
-// or beyond L read level L - 1), its weight and its entry.
-template <typename TF, int F>
-__device__ __forceinline__ void lat_corner(const Geom &g, const TF *__restrict__ tab, int l, uint32_t c,
-                                           const float p[3], float &wc, Entry<TF, F> &en)
-{
-    const int lc = l < g.L ? l : g.L - 1;
-    uint32_t i[3];
-    float wt[3];
-    level_cell_mm(g, lc, p, i, wt);
-    const uint32_t x = i[0] + (c & 1u), y = (i[1] + ((c >> 1) & 1u)) * g.my[lc], z = (i[2] + (c >> 2)) * g.mz[lc];
-    const uint32_t s = ((x + y + z) & g.dmask[lc]) | ((x ^ y ^ z) & g.hmask[lc]);
-    const float wx = (c & 1u) ? wt[0] : 1.0f - wt[0];
-    const float wy = ((c >> 1) & 1u) ? wt[1] : 1.0f - wt[1];
-    const float wz = (c >> 2) ? wt[2] : 1.0f - wt[2];
-    wc = wx * (wy * wz);
-    en.load(reinterpret_cast<const char *>(tab + ((size_t)lc << g.log2_T) * F), s * (uint32_t)(F * sizeof(TF)));
-}
-
-template <int F>
-__global__ __launch_bounds__(64 * kLatWaves) void k_query_lat(QueryArgs A)
-{
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t slot = A.tile0 * kBlock + blockIdx.x * kLatWaves + (threadIdx.x >> 6);
-    if (slot >= A.n) return;   // the whole wave
-    const Geom &g = A.g;
-    const Mlp &mm = A.m;
-    const float *__restrict__ tab = reinterpret_cast<const float *>(A.tables);
-    const float *__restrict__ W = reinterpret_cast<const float *>(mm.W);
-    uint32_t r, pair;
-    bool live;
-    VRay w;
-    slot_ray<false>(A, g, slot, r, pair, live, w);
-    const int count = __builtin_amdgcn_readfirstlane(live ? 2 * (int)A.nvox[slot] : 0);
-    const int LF = g.L * F;
-    const uint32_t q = lane >> 3, c = lane & 7u;
-    float acc = 0.0f;
-    float fv[2][F];   // this lane's level features (rounds 0 and 1), kept for a repeated point
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int f = 0; f < F; ++f) fv[k][f] = 0.0f;
-    uint32_t pp[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu};
-    int pface = -1;
-    float amax = 0.0f;   // largest |input| of the current layer (calibration)
-    for (int h = 0; h < count; ++h) {
-        // this point's layer-1 weights (output `lane` of each input), requested ahead of the gathers
-        float wk[kLatMaxLF];
-        const float *W1 = W + mm.off[0] + (size_t)h * LF * 64 + lane;
-#pragma unroll
-        for (int k = 0; k < kLatMaxLF; ++k) wk[k] = W1[(size_t)(k < LF ? k : 0) * 64];   // k >= LF: unused
-        float p[3];
-        const int face = boundary_point(w, A.lists[(size_t)(h >> 1) * A.n + slot], h & 1, p);
-        const bool dup = (h & 1) == 0 && face == pface && __float_as_uint(p[0]) == pp[0] &&
-                         __float_as_uint(p[1]) == pp[1] && __float_as_uint(p[2]) == pp[2];
-        if (!dup) {
-            lat_level<float, F>(g, tab, (int)q, c, p, fv[0]);
-            if (g.L > 8) lat_level<float, F>(g, tab, 8 + (int)q, c, p, fv[1]);
-        }
-        if (A.dbg.act_amax) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-                for (int f = 0; f < F; ++f) amax = fmax2(amax, __builtin_fabsf(fv[k][f]));
-        }
-        if (A.dbg.enc && live && c == 0u) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int l = 8 * k + (int)q;
-                if (l < g.L)
-#pragma unroll
-                    for (int f = 0; f < F; ++f) A.dbg.enc[((size_t)r * g.H + h) * LF + l * F + f] = fv[k][f];
-            }
-        }
-        // input k = l F + f lives in lane 8 (l mod 8), round l / 8
-#pragma unroll
-        for (int k = 0; k < kLatMaxLF; ++k) {
-            if (k < LF) {
-                const int l = k / F, f = k % F;
-                const float x = __builtin_bit_cast(
-                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, fv[l >> 3][f]), 8 * (l & 7)));
-                acc = __builtin_fmaf(wk[k], x, acc);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < 3; ++b) pp[b] = __float_as_uint(p[b]);
-        pface = face;
-    }
-    // hidden layers, then the head (lanes below kMaxOut)
-    float o = 0.0f;
-    if (A.dbg.act_amax) fold_max(A.dbg.act_amax + 0, amax);
-    if (count > 0) {
-        for (int k = 1; k <= mm.n_hidden; ++k) {
-            const bool head = k == mm.n_hidden;
-            const float x = act_f(acc, mm.act, mm.slope);
-            if (A.dbg.act_amax) fold_max(A.dbg.act_amax + k, __builtin_fabsf(x));
-            const float *Wk = W + mm.off[k] + (head ? (lane < (uint32_t)kMaxOut ? lane : 0u) : lane);
-            const int stride = head ? kMaxOut : 64;
-            float nxt = 0.0f;
-#pragma unroll 16
-            for (int i = 0; i < 64; ++i) {
-                const float xi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i));
-                nxt = __builtin_fmaf(Wk[(size_t)i * stride], xi, nxt);
-            }
-            if (head) o = lane < (uint32_t)kMaxOut ? nxt : 0.0f;
-            else acc = nxt;
-        }
-    }
-    float oo[kMaxOut];
-#pragma unroll
-    for (int k = 0; k < kMaxOut; ++k)
-        oo[k] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, o), k));
-    if (!live || lane != 0u) return;
-    if (A.dbg.count) A.dbg.count[r] = w.valid ? count : -1;
-    if (A.dbg.tatb) {
-        A.dbg.tatb[2 * r] = w.ta;
-        A.dbg.tatb[2 * r + 1] = w.tb;
-    }
-    if (A.dbg.out) {
-#pragma unroll
-        for (int k = 0; k < kMaxOut; ++k)
-            if (k < mm.out_dim) A.dbg.out[(size_t)r * mm.out_dim + k] = count > 0 ? oo[k] : 0.0f;
-    }
-    decode_store<false>(A, mm, r, pair, w, count, oo);
-}
-
-// The matrix-core form of the one-wave-per-ray kernel (two features per level,
-// width 64, at most two K blocks per point).  The wave's lanes interpolate the
-// ray's point as above; every lane then packs the point's 16 K slots of a K
-// block, and the B operand puts slots 0..7 in lanes 0..31 and 8..15 in lanes
-// 32..63, so each of the 32 columns is this ray.  A column of a matrix-core
-// product does not depend on the other columns, so every column, and the
-// answer, has the bits the ray gets in k_query_mma.
-template <typename TF, typename TM, int KBM>
-__global__ __launch_bounds__(64 * kLatWaves) void k_query_mma_lat(QueryArgs A)
-{
-    typedef typename MmaT<TM>::vec vec_t;
-    constexpr int F = 2, MB = 2, DW = MmaT<TM>::DW;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t slot = A.tile0 * kBlock + blockIdx.x * kLatWaves + (threadIdx.x >> 6);
-    if (slot >= A.n) return;   // the whole wave
-    const Geom &g = A.g;
-    const Mlp &mm = A.m;
-    const TF *__restrict__ tab = reinterpret_cast<const TF *>(A.tables);
-    const uint32_t *__restrict__ Wv = reinterpret_cast<const uint32_t *>(mm.W);
-    uint32_t r, pair;
-    bool live;
-    VRay w;
-    slot_ray<false>(A, g, slot, r, pair, live, w);
-    const int count = __builtin_amdgcn_readfirstlane(live ? 2 * (int)A.nvox[slot] : 0);
-    const int KB = mm.kb_point;
-    const uint32_t q = lane >> 3, c = lane & 7u;
-    f16_t acc[MB];
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[m][e] = 0.0f;
-    uint32_t prev[KBM][DW];
-#pragma unroll
-    for (int kb = 0; kb < KBM; ++kb)
-#pragma unroll
-        for (int d = 0; d < DW; ++d) prev[kb][d] = 0u;
-    uint32_t pp[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu};
-    int pface = -1;
-    for (int h = 0; h < count; ++h) {
-        // the point's layer-1 weight fragments, requested ahead of the gathers
-        uint32_t wd[KBM][MB][DW];
-#pragma unroll
-        for (int kb = 0; kb < KBM; ++kb)
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-                load_frag<DW>(Wv + mm.woff[0] + ((size_t)(((h * KB + (kb < KB ? kb : 0)) * MB + m) * 64) + lane) * DW,
-                              wd[kb][m]);
-        float p[3];
-        const int face = boundary_point(w, A.lists[(size_t)(h >> 1) * A.n + slot], h & 1, p);
-        const bool dup = (h & 1) == 0 && face == pface && __float_as_uint(p[0]) == pp[0] &&
-                         __float_as_uint(p[1]) == pp[1] && __float_as_uint(p[2]) == pp[2];
-        // this lane's corner: c of level 8 kb + q, for the two K blocks
-        float wcr[2] = {0.0f, 0.0f};
-        Entry<TF, F> enr[2];
-        if (!dup) {
-            lat_corner<TF, F>(g, tab, (int)q, c, p, wcr[0], enr[0]);
-            if (g.L > 8) lat_corner<TF, F>(g, tab, 8 + (int)q, c, p, wcr[1], enr[1]);
-        }
-        const uint32_t hf = lane >> 5;
-#pragma unroll
-        for (int kb = 0; kb < KBM; ++kb) {
-            if (kb >= KB) break;
-            uint32_t bk[DW];
-            if (!dup) {
-                // Lanes 0..31 form the B operand's K slots 0..7 (levels 8 kb .. 8 kb + 3), lanes
-                // 32..63 slots 8..15 (levels 8 kb + 4 .. 8 kb + 7): each lane sums those 4 levels'
-                // corners itself, in corner order, and packs them, as a lane of k_query_mma
-                // does for its own ray (the same expressions, so the same roundings).
-                float e[8];
-#pragma unroll
-                for (int li = 0; li < 4; ++li) {
-                    const int j = 4 * (int)hf + li;   // level 8 kb + j: corners in lanes 8 j ..
-                    float v[F];
-#pragma unroll
-                    for (int f = 0; f < F; ++f) v[f] = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const float wk = __shfl(wcr[kb], 8 * j + k, 64);
-                        Entry<TF, F> ek;
-#pragma unroll
-                        for (int d = 0; d < Entry<TF, F>::W; ++d)
-                            ek.d[d] = (uint32_t)__shfl((int)enr[kb].d[d], 8 * j + k, 64);
-#pragma unroll
-                        for (int f = 0; f < F; ++f) v[f] = __builtin_fmaf(wk, ek.get(f), v[f]);
-                    }
-                    if (8 * kb + j >= g.L) {
-#pragma unroll
-                        for (int f = 0; f < F; ++f) v[f] = 0.0f;
-                    }
-#pragma unroll
-                    for (int f = 0; f < F; ++f) e[2 * li + f] = v[f];
-                }
-                pack8<TM>(e, mm.qs[0], bk);
-            } else {
-#pragma unroll
-                for (int d = 0; d < DW; ++d) bk[d] = prev[kb][d];
-            }
-            if (A.dbg.enc && live && (lane & 31u) == 0u) {
-                // lane 0 writes K slots 0..7, lane 32 slots 8..15 (a repeated point: the previous one's)
-                const int LF = g.L * F;
-                for (int k = 0; k < 8; ++k) {
-                    const int l = kb * 8 + 4 * (int)hf + k / 2, f = k % 2;
-                    if (l < g.L) {
-                        const float v = unpack8<TM>(bk, k);
-                        A.dbg.enc[(size_t)r * g.H * LF + h * LF + l * F + f] = MmaT<TM>::scaled ? v / mm.qs[0] : v;
-                    }
-                }
-            }
-#pragma unroll
-            for (int d = 0; d < DW; ++d) prev[kb][d] = bk[d];
-            const vec_t b0 = as_vec<vec_t, DW>(bk);
-#pragma unroll
-            for (int m = 0; m < MB; ++m) acc[m] = MmaT<TM>::mma(as_vec<vec_t, DW>(wd[kb][m]), b0, acc[m]);
-        }
-#pragma unroll
-        for (int b = 0; b < 3; ++b) pp[b] = __float_as_uint(p[b]);
-        pface = face;
-    }
-    // hidden layers 2..n_hidden, then the head, as k_query_mma with one column block
-    float o[kMaxOut];
-#pragma unroll
-    for (int k = 0; k < kMaxOut; ++k) o[k] = 0.0f;
-    if (count > 0) {
-        for (int k = 1; k <= mm.n_hidden; ++k) {
-            const bool head = k == mm.n_hidden;
-            const float dqi = mm.dq[k - 1], qsi = mm.qs[k];
-            uint32_t xb[MB][2][DW];
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-#pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2) {
-                    float v[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float y = MmaT<TM>::scaled ? acc[m][8 * s2 + e] * dqi : acc[m][8 * s2 + e];
-                        v[e] = act_f(y, mm.act, mm.slope);
-                    }
-                    pack8<TM>(v, qsi, xb[m][s2]);
-                }
-            const int MO = head ? 1 : MB;
-            const uint32_t *Wk = Wv + mm.woff[k] + (size_t)lane * DW;
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[m][e] = 0.0f;
-#pragma unroll
-            for (int mo = 0; mo < MB; ++mo) {
-                if (mo < MO) {
-#pragma unroll
-                    for (int m = 0; m < MB; ++m)
-#pragma unroll
-                        for (int s2 = 0; s2 < 2; ++s2) {
-                            uint32_t wd2[DW];
-                            load_frag<DW>(Wk + (size_t)((mo * MB + m) * 2 + s2) * 64 * DW, wd2);
-                            acc[mo] = MmaT<TM>::mma(as_vec<vec_t, DW>(wd2), as_vec<vec_t, DW>(xb[m][s2]), acc[mo]);
-                        }
-                }
-            }
-        }
-        // rows 8q + r of the head lie in lanes 0..31, rows 8q + 4 + r in lanes 32..63
-        uint32_t x[8], y[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            x[e] = __float_as_uint(acc[0][e]);
-            y[e] = x[e];
-            swap32(x[e], y[e]);
-        }
-        const float dqo = MmaT<TM>::scaled ? mm.dq[mm.n_hidden] : 1.0f;
-#pragma unroll
-        for (int q2 = 0; q2 < 2; ++q2)
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                o[8 * q2 + rr] = __uint_as_float(x[4 * q2 + rr]) * dqo;
-                o[8 * q2 + 4 + rr] = __uint_as_float(y[4 * q2 + rr]) * dqo;
-            }
-    }
-    if (!live || lane != 0u) return;
-    if (A.dbg.count) A.dbg.count[r] = w.valid ? count : -1;
-    if (A.dbg.tatb) {
-        A.dbg.tatb[2 * r] = w.ta;
-        A.dbg.tatb[2 * r + 1] = w.tb;
-    }
-    if (A.dbg.out) {
-#pragma unroll
-        for (int k = 0; k < kMaxOut; ++k)
-            if (k < mm.out_dim) A.dbg.out[(size_t)r * mm.out_dim + k] = count > 0 ? o[k] : 0.0f;
-    }
-    decode_store<false>(A, mm, r, pair, w, count, o);
-}
-
 // ------------------------------------------------------------- gather ceiling
 //
 // The query kernel's gathers alone, for measurement: the same prologue (voxel
@@ -1576,7 +713,7 @@ __device__ __forceinline__ void gather_only_body(const QueryArgs &A, float *sums
         if (has && !dup) {
             for (int l0 = 0; l0 < g.L; l0 += NL) {
                 float v[NL][F];
-                encode_levels<TF, F, NL, false>(g, tab, nullptr, l0, p, face, v);
+                encode_levels<TF, F, NL>(g, tab, l0, p, face, v);
 #pragma unroll
                 for (int lv = 0; lv < NL; ++lv)
 #pragma unroll

@@ -31,21 +31,11 @@ __host__ __device__ inline size_t radix_ws_words(uint32_t n) { return 4u * (size
 struct Geom;
 struct QueryArgs;
 struct DebugArgs;
-// Query kernels: `grid` blocks of 256 lanes; `pairs` selects the instanced-pair variant.
-hipError_t launch_f32(const QueryArgs &A, int feat_dtype, int F, bool pairs, uint32_t grid, hipStream_t s);
-// One wave per ray (FP32 features and MLP, width 64, F <= 3, at most 16 levels), for `grid`
-// tiles' slots starting at tile A.tile0.
-hipError_t launch_lat(const QueryArgs &A, int F, uint32_t grid, hipStream_t s);
-// The same with the MLP on the matrix cores (two features per level, at most two K blocks).
-hipError_t launch_mma_small_f16(const QueryArgs &A, int feat_dtype, int kbm, uint32_t grid, hipStream_t s);
-hipError_t launch_mma_small_bf16(const QueryArgs &A, int feat_dtype, int kbm, uint32_t grid, hipStream_t s);
-hipError_t launch_mma_small_fp8(const QueryArgs &A, int feat_dtype, int kbm, uint32_t grid, hipStream_t s);
-hipError_t launch_mma_f16(const QueryArgs &A, int feat_dtype, int F, int kbm, bool pairs, uint32_t grid,
-                          hipStream_t s);
-hipError_t launch_mma_bf16(const QueryArgs &A, int feat_dtype, int F, int kbm, bool pairs, uint32_t grid,
-                           hipStream_t s);
-hipError_t launch_mma_fp8(const QueryArgs &A, int feat_dtype, int F, int kbm, bool pairs, uint32_t grid,
-                          hipStream_t s);
+// The query kernel over `grid` tiles of 256 slots, by MLP type; max_L: the most levels of its objects.
+hipError_t launch_query_f32(const QueryArgs &A, int feat_dtype, int F, int max_L, bool pairs, uint32_t grid, hipStream_t s);
+hipError_t launch_query_f16(const QueryArgs &A, int feat_dtype, int F, int max_L, bool pairs, uint32_t grid, hipStream_t s);
+hipError_t launch_query_bf16(const QueryArgs &A, int feat_dtype, int F, int max_L, bool pairs, uint32_t grid, hipStream_t s);
+hipError_t launch_query_fp8(const QueryArgs &A, int feat_dtype, int F, int max_L, bool pairs, uint32_t grid, hipStream_t s);
 // Voxel walk of every slot into A.lists / A.nvox, before the query kernel of the same `grid`;
 // `recheck` when some object of the launch re-decides grazing voxels in float64; max_V: the
 // largest grid of its objects.
@@ -63,11 +53,6 @@ hipError_t launch_broad_write(const BroadArgs &B, hipStream_t s);
 struct BounceArgs;
 hipError_t launch_bounce_mark(const BounceArgs &B, hipStream_t s);
 hipError_t launch_bounce_write(const BounceArgs &B, hipStream_t s);
-// Persistent query kernels: zero the 8 tile-queue counters at q (one 256-byte granule),
-// and the grid for `kernel` with `lds` dynamic bytes: as many blocks as the chip holds at
-// once (a multiple of 8, one per XCD in turn), at most the launch's tiles rounded up to 8.
-hipError_t launch_clear_queue(unsigned long long *q, hipStream_t s);
-uint32_t persistent_blocks(const void *kernel, size_t lds, uint32_t tiles);
 // In-place exclusive scan of n counters; `part` holds (n + 1023) / 1024 partial sums.
 hipError_t launch_exclusive_scan(uint32_t *v, uint32_t n, uint32_t *part, hipStream_t s);
 // Merged serving launches: stage the members' rays and re-indexed pairs, and copy the

@@ -4,8 +4,8 @@
 //
 // Every candidate runs the real query on the caller's batch (one warm-up, then
 // three timed queries between HIP events on a private stream), so the choice
-// reflects the batch's own coherence, the object's table sizes and the LDS
-// left for hot levels.  None of the parameters changes a result.
+// reflects the batch's own coherence and the object's table sizes.  None of the
+// parameters changes a result.
 
 #include <hip/hip_runtime.h>
 
@@ -36,7 +36,6 @@ void apply_tuning(lsnif_ctx *ctx, Object &ob, const lsnif_tuning &t)
     ob.hot_budget = (uint32_t)t.hot_lds_bytes;
     ob.walk_chunks = (uint32_t)t.walk_chunks;
     ob.persistent = (uint32_t)t.persistent;
-    plan_hot_levels(ob.geom, ob.esz, ob.hot_budget);
     ctx->table_dirty = true;
     ++ctx->generation;
 }
@@ -91,7 +90,6 @@ template <typename Fn> lsnif_status with_stream(Fn &&fn)
     return st;
 }
 
-const int32_t kHotCandidates[] = {0, 20 << 10, 40 << 10};
 const int32_t kChunkCandidates[] = {1, 2, 4, 8};
 
 }  // namespace
@@ -156,18 +154,16 @@ lsnif_status lsnif_autotune(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray 
             return LSNIF_OK;
         };
         for (int sb : {0, 4, 5, 6, 7})
-            for (int32_t hot : kHotCandidates)
-                if (lsnif_status e = run(lsnif_tuning{sb, start.pair_bits, hot, start.walk_chunks, start.persistent}))
-                    return e;
+            if (lsnif_status e = run(lsnif_tuning{sb, start.pair_bits, start.hot_lds_bytes, start.walk_chunks,
+                                                  start.persistent}))
+                return e;
         const lsnif_tuning best = win;
         for (int32_t ch : kChunkCandidates)
             if (ch != best.walk_chunks)
                 if (lsnif_status e = run(lsnif_tuning{best.sort_bits, best.pair_bits, best.hot_lds_bytes, ch,
                                                       best.persistent}))
                     return e;
-        lsnif_tuning flip = win;
-        flip.persistent = 1 - flip.persistent;
-        return run(flip);
+        return LSNIF_OK;
     });
     apply(ctx, ob, st ? start : win);
     if (st) return st;
@@ -200,6 +196,7 @@ lsnif_status lsnif_autotune_pairs(lsnif_ctx *ctx, const lsnif_ray *d_rays, uint3
     lsnif_tuning win{};
     float win_ms = -1.0f;
     const uint32_t start_chunks = ctx->objects.begin()->second.walk_chunks;
+    const int32_t start_hot = (int32_t)ctx->objects.begin()->second.hot_budget;
     const int32_t start_persist = (int32_t)ctx->objects.begin()->second.persistent;
     lsnif_status st = with_stream([&](hipStream_t s, hipEvent_t e0, hipEvent_t e1) -> lsnif_status {
         auto run = [&](const lsnif_tuning &t) -> lsnif_status {
@@ -225,16 +222,13 @@ lsnif_status lsnif_autotune_pairs(lsnif_ctx *ctx, const lsnif_ray *d_rays, uint3
             return LSNIF_OK;
         };
         for (int pb : {2, 3, 4, 5, 6})
-            for (int32_t hot : kHotCandidates)
-                if (lsnif_status e = run(lsnif_tuning{0, pb, hot, (int32_t)start_chunks, start_persist})) return e;
+            if (lsnif_status e = run(lsnif_tuning{0, pb, start_hot, (int32_t)start_chunks, start_persist})) return e;
         const lsnif_tuning best = win;
         for (int32_t ch : kChunkCandidates)
             if (ch != best.walk_chunks)
                 if (lsnif_status e = run(lsnif_tuning{0, best.pair_bits, best.hot_lds_bytes, ch, best.persistent}))
                     return e;
-        lsnif_tuning flip = win;
-        flip.persistent = 1 - flip.persistent;
-        return run(flip);
+        return LSNIF_OK;
     });
     if (st) {
         for (auto &p : start) apply(ctx, ctx->objects[p.first], p.second);
