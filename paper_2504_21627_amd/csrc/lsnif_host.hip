@@ -358,6 +358,7 @@ lsnif_status lsnif_build(lsnif_ctx *ctx, const lsnif_object_desc *d, uint32_t *o
         ob.hot_budget = (uint32_t)cached->second.hot_lds_bytes;
         ob.walk_chunks = (uint32_t)cached->second.walk_chunks;
         ob.persistent = (uint32_t)cached->second.persistent;
+        ob.tuned = true;
     }
     // occupancy as 4x4x4 bricks: one 64-bit mask per brick, then one bit per brick
     const int V = d->V, NB = (V + 3) / 4;
@@ -731,7 +732,7 @@ lsnif_status enqueue_query(lsnif_ctx *ctx, const Object &ob, const lsnif_ray *d_
             if (!(e = take_event(ctx))) return fail(LSNIF_E_DEVICE, "hipEventCreate failed");
         HIP_TRY(hipEventRecord(ev[0], s));
     }
-    const size_t sort_bytes = sort_ws_bytes(n, ob.geom.sort_bits);
+    const size_t sort_bytes = sort_ws_bytes(n, ob.query_sort_bits());
     if (sort_bytes) {
         uint32_t *order = nullptr;
         HIP_TRY(launch_coherence_sort(ob.geom, A.rays, n, static_cast<uint32_t *>(ws), &order, s));

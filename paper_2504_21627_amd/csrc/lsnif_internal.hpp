@@ -31,6 +31,15 @@ lsnif_status fail(lsnif_status st, const char *fmt, ...);
 constexpr uint32_t kWalkChunks = 1;
 constexpr uint32_t kMinChunkTiles = 256;
 
+// Batches below this size are processed in the order given (no coherence sort).
+constexpr uint32_t kSortMin = 8192;
+// So are, unless a tuning says otherwise, batches on objects whose tables fit the 4 MiB of
+// one XCD's L2: the sort then costs more than what its order saves.  Measured (us per call,
+// sorted / as given): tables of 1 MiB 40,000 rays 129 / 73, 1,500,000 549 / 467; 1.5 MiB
+// 300,000 bounce rays 224 / 168; 3 MiB 262,144 rays 474 / 398 and 297 / 273.  With 32 MiB the
+// order is worth 0.6 ms of 1.3 at 200,000 rays.
+constexpr uint64_t kSortTables = 4u << 20;
+
 struct Object {
     Geom geom{};
     Mlp mlp{};
@@ -39,7 +48,14 @@ struct Object {
     uint32_t hot_budget = 0;      // the tuning's hot_lds_bytes and persistent: kept and reported, nothing reads them
     uint32_t walk_chunks = kWalkChunks;    // tile ranges of a query whose walk runs ahead
     uint32_t persistent = 0;
+    bool tuned = false;           // sort_bits was set, found or cached for the object
     uint64_t bytes = 0;
+    // bits of the coherence sort that a query of the object runs (0: none)
+    uint32_t query_sort_bits() const
+    {
+        const uint64_t tables = ((uint64_t)geom.L << geom.log2_T) * (uint64_t)F * (feat_dtype == LSNIF_FP32 ? 4u : 2u);
+        return tuned || tables > kSortTables ? geom.sort_bits : 0u;
+    }
 };
 
 // Objects that one query kernel can serve together.
@@ -64,9 +80,6 @@ struct DeviceGuard {
 
 class Server;
 void destroy_server(lsnif_ctx *ctx);   // stops a running serving loop
-
-// Batches below this size are processed in the order given (no coherence sort).
-constexpr uint32_t kSortMin = 8192;
 
 // Workspace bytes of one query of n rays, and of one pair query; cap is the
 // longest voxel list (H / 2, the largest over the objects for pairs).

@@ -119,6 +119,7 @@ lsnif_status lsnif_set_tuning(lsnif_ctx *ctx, uint32_t object_id, const lsnif_tu
         HIP_TRY(hipDeviceSynchronize());   // queries in flight read the old parameters by value
     }
     apply(ctx, it->second, *tuning);
+    it->second.tuned = true;
     return LSNIF_OK;
 }
 
@@ -137,8 +138,10 @@ lsnif_status lsnif_autotune(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray 
     if ((st = grow_workspace(ctx->ws, ctx->ws_bytes, query_ws_bytes(n, 7, ob.geom.H >> 1)))) return st;   // the most bins
     HIP_TRY(hipDeviceSynchronize());
     const lsnif_tuning start = current(ob);
+    const bool was_tuned = ob.tuned;
     lsnif_tuning win = start;
     float win_ms = -1.0f;
+    ob.tuned = true;   // the candidates' sort_bits hold
     st = with_stream([&](hipStream_t s, hipEvent_t e0, hipEvent_t e1) -> lsnif_status {
         auto run = [&](const lsnif_tuning &t) -> lsnif_status {
             apply(ctx, ob, t);
@@ -166,7 +169,10 @@ lsnif_status lsnif_autotune(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray 
         return LSNIF_OK;
     });
     apply(ctx, ob, st ? start : win);
-    if (st) return st;
+    if (st) {
+        ob.tuned = was_tuned;
+        return st;
+    }
     *best = win;
     if (ctx->cache_path.empty()) return LSNIF_OK;
     ctx->cache[cache_key(ctx, ob)] = win;
