@@ -149,18 +149,17 @@ template <typename TF, int F> struct Entry {
         } else if constexpr (F * sizeof(TF) == 16) {
             uint4 x = *reinterpret_cast<const uint4 *>(base + off);
             d[0] = x.x; d[1] = x.y; d[2] = x.z; d[3] = x.w;
+        } else if constexpr (F == 3 && sizeof(TF) == 2) {
+            // one 8-byte load from a 2-byte boundary: the 6 bytes and 2 that nothing reads (after
+            // the last entry, spare ones)
+            typedef uint32_t u32x2a2 __attribute__((ext_vector_type(2), aligned(2)));
+            const u32x2a2 x = *reinterpret_cast<const u32x2a2 *>(base + off);
+            d[0] = x.x;
+            d[1] = x.y;
         } else {
-            const TF *p = reinterpret_cast<const TF *>(base + off);
-            uint16_t u[2 * W] = {};
-            float f32[W] = {};
-            for (int f = 0; f < F; ++f) {
-                if constexpr (sizeof(TF) == 2) __builtin_memcpy(&u[f], &p[f], 2);
-                else f32[f] = to_f32<TF>(p[f]);
-            }
-            for (int k = 0; k < W; ++k) {
-                if constexpr (sizeof(TF) == 2) d[k] = (uint32_t)u[2 * k] | ((uint32_t)u[2 * k + 1] << 16);
-                else d[k] = __float_as_uint(f32[k]);
-            }
+            static_assert(F == 3 && sizeof(TF) == 4, "2 or 3 features");
+            const uint32_t *x = reinterpret_cast<const uint32_t *>(base + off);
+            d[0] = x[0]; d[1] = x[1]; d[2] = x[2];
         }
     }
     // An opaque use of the loaded dwords: nothing that reads them can be
@@ -191,13 +190,27 @@ __device__ __forceinline__ void level_cell_mm(const Geom &g, int l, const float 
     }
 }
 
+// The last multiply-add of a sum that is rounded to FP16 next.  In one instruction the two
+// are one rounding; the compiler finds it only where both lie in one basic block, so a
+// caller with several ways to the rounding takes it here (the result is exact in float).
+__device__ __forceinline__ float fma_f16(float a, float b, float c)
+{
+    const _Float16 h = (_Float16)__builtin_fmaf(a, b, c);
+    uint16_t u;
+    __builtin_memcpy(&u, &h, 2);
+    uint32_t x = u;
+    asm volatile("" : "+v"(x));   // keeps both halves here
+    return lo16<_Float16>(x);
+}
+
 // Interpolated features of NL consecutive levels l0 .. l0 + NL - 1 at the
 // boundary point p (voxel units) whose crossing axis is `face`; levels at or
 // beyond L give zeros.  All slots are formed first and all gathers issued
 // before any is consumed.  On a level aligned with the voxel faces the
 // crossing-axis weight is exactly 0 or 1, and the 4 zero-weight corners do
 // not touch their own entries (they read the level's first entry).
-template <typename TF, int F, int NL>
+// H16: the features are rounded to FP16 (fma_f16).
+template <typename TF, int F, int NL, bool H16 = false>
 __device__ __forceinline__ void encode_levels(const Geom &g, const TF *__restrict__ tab, int l0, const float p[3],
                                               int face, float out[NL][F])
 {
@@ -286,8 +299,80 @@ __device__ __forceinline__ void encode_levels(const Geom &g, const TF *__restric
             for (int xb = 0; xb < 2; ++xb) {
                 const float w = wx[lv][xb] * wyz;
 #pragma unroll
-                for (int f = 0; f < F; ++f) out[lv][f] = __builtin_fmaf(w, e[lv][2 * q + xb].get(f), out[lv][f]);
+                for (int f = 0; f < F; ++f) {
+                    const float x = e[lv][2 * q + xb].get(f);
+                    out[lv][f] = H16 && q == 3 && xb == 1 ? fma_f16(w, x, out[lv][f]) : __builtin_fmaf(w, x, out[lv][f]);
+                }
             }
+        }
+        if (l0 + lv >= g.L) {
+#pragma unroll
+            for (int f = 0; f < F; ++f) out[lv][f] = 0.0f;
+        }
+    }
+}
+
+// encode_levels for levels that are all aligned with the voxel faces: the crossing-axis
+// weight of a boundary point is exactly 0 or 1 there, so the features are sums over the
+// 4 corners of its face.  encode_levels' 4 other corners weigh 0 and leave its sum as it
+// is; its last addition (corner 7) may be rounded together with the conversion of the sum,
+// so the last addition here is the fourth corner's where that is corner 7, and one of 0
+// where it is not.
+template <typename TF, int F, int NL, bool H16>
+__device__ __forceinline__ void encode_aligned(const Geom &g, const TF *__restrict__ tab, int l0, const float p[3],
+                                               int face, float out[NL][F])
+{
+    constexpr uint32_t esz = F * sizeof(TF);
+    constexpr uint32_t sh = esz == 4 ? 2u : (esz == 8 ? 3u : (esz == 16 ? 4u : 0u));
+    constexpr uint32_t m = sh ? 1u : esz;
+    Entry<TF, F> e[NL][4];
+    float wu[NL], wv[NL];
+    bool up[NL];
+#pragma unroll
+    for (int lv = 0; lv < NL; ++lv) {
+        const int l = l0 + lv < g.L ? l0 + lv : g.L - 1;
+        uint32_t i[3];
+        float wt[3];
+        level_cell_mm(g, l, p, i, wt);
+        const uint32_t my = g.my[l] << sh, mz = g.mz[l] << sh;
+        const uint32_t x0 = i[0] << sh, x1 = x0 + (1u << sh), y0 = i[1] * my, y1 = y0 + my, z0 = i[2] * mz, z1 = z0 + mz;
+        // u, v: the axes of the face, in order; f: the face's vertex on the crossing axis
+        up[lv] = (face == 0 ? wt[0] : (face == 1 ? wt[1] : wt[2])) != 0.0f;
+        const uint32_t f0 = face == 0 ? x0 : (face == 1 ? y0 : z0), f1 = face == 0 ? x1 : (face == 1 ? y1 : z1);
+        const uint32_t f = up[lv] ? f1 : f0;
+        const uint32_t u[2] = {face == 0 ? y0 : x0, face == 0 ? y1 : x1};
+        const uint32_t v[2] = {face == 2 ? y0 : z0, face == 2 ? y1 : z1};
+        wu[lv] = face == 0 ? wt[1] : wt[0];
+        wv[lv] = face == 2 ? wt[1] : wt[2];
+        const char *base = reinterpret_cast<const char *>(tab + ((size_t)l << g.log2_T) * F);
+        uint32_t off[4];
+        if ((g.dense_mask >> l) & 1u) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) off[q] = (f + u[q & 1] + v[q >> 1]) * m;
+        } else {
+            const uint32_t hm = g.hmask[l] << sh;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) off[q] = ((f ^ u[q & 1] ^ v[q >> 1]) & hm) * m;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) e[lv][q].load(base, off[q]);
+    }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int lv = 0; lv < NL; ++lv)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) e[lv][q].pin();
+#pragma unroll
+    for (int lv = 0; lv < NL; ++lv) {
+        const float u0 = 1.0f - wu[lv], u1 = wu[lv], v0 = 1.0f - wv[lv], v1 = wv[lv];
+        const float w3 = u1 * v1, wl = up[lv] ? w3 : 0.0f;
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            float s = __builtin_fmaf(u0 * v0, e[lv][0].get(f), 0.0f);
+            s = __builtin_fmaf(u1 * v0, e[lv][1].get(f), s);
+            s = __builtin_fmaf(u0 * v1, e[lv][2].get(f), s);
+            const float a = up[lv] ? s : __builtin_fmaf(w3, e[lv][3].get(f), s);
+            out[lv][f] = H16 ? fma_f16(wl, e[lv][3].get(f), a) : __builtin_fmaf(wl, e[lv][3].get(f), a);
         }
         if (l0 + lv >= g.L) {
 #pragma unroll

@@ -227,8 +227,17 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
             if (s < npts) {
                 const float4 p4 = pts[s];
                 const float p[3] = {p4.x, p4.y, p4.z};
+                const int l0 = (int)(b * P::NLB);
                 float v[P::NLB][F];
-                encode_levels<TF, F, P::NLB>(g, tab, (int)(b * P::NLB), p, __float_as_int(p4.w), v);
+                bool aligned = false;
+                if constexpr (F == 3) {
+                    const uint32_t all = ((1u << P::NLB) - 1u) & ((uint32_t)(2u << (g.L - 1 - l0)) - 1u);
+                    aligned = (~(g.aligned_mask >> l0) & all) == 0u;
+                }
+                // two ways to the rounding (F = 3): see fma_f16
+                constexpr bool H16 = F == 3 && __is_same(TM, _Float16);
+                if (aligned) encode_aligned<TF, F, P::NLB, H16>(g, tab, l0, p, __float_as_int(p4.w), v);
+                else encode_levels<TF, F, P::NLB, H16>(g, tab, l0, p, __float_as_int(p4.w), v);
                 if constexpr (f32) {
                     float *d = reinterpret_cast<float *>(lds + s * pb);
 #pragma unroll

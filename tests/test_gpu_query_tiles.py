@@ -16,13 +16,16 @@ pytestmark = pytest.mark.gpu
 
 U = {"fp32": 2.0 ** -24, "fp16": 2.0 ** -11, "bf16": 2.0 ** -8, "fp8": 2.0 ** -4}
 
-# feat, mlp, F, L, width, H, V, density of occupied voxels
+# feat, mlp, F, L, width, H, V, density of occupied voxels[, the levels aligned with the faces]
 CASES = [("fp32", "fp32", 2, 1, 64, 18, 8, 0.5), ("fp32", "fp32", 3, 5, 128, 18, 16, 0.5),
          ("fp16", "fp32", 2, 9, 64, 64, 32, 0.9), ("fp32", "fp32", 3, 32, 64, 18, 8, 0.4),
          ("fp16", "fp16", 2, 1, 64, 2, 8, 0.5), ("fp16", "fp16", 2, 5, 64, 18, 16, 0.3),
          ("fp16", "fp16", 3, 3, 128, 18, 16, 0.5), ("bf16", "bf16", 2, 13, 64, 64, 32, 0.9),
          ("fp32", "fp16", 2, 16, 128, 18, 16, 0.2), ("fp16", "fp16", 3, 32, 64, 18, 8, 0.4),
-         ("fp16", "fp8", 2, 7, 64, 18, 16, 0.5), ("bf16", "fp8", 3, 5, 128, 18, 16, 0.5)]
+         ("fp16", "fp8", 2, 7, 64, 18, 16, 0.5), ("bf16", "fp8", 3, 5, 128, 18, 16, 0.5),
+         ("fp16", "fp16", 3, 3, 128, 18, 16, 0.5, "all"), ("fp32", "fp32", 3, 3, 64, 18, 16, 0.5, "all"),
+         ("fp16", "fp16", 3, 4, 64, 18, 16, 0.5, "even"), ("bf16", "fp32", 3, 4, 128, 18, 16, 0.5, "even")]
+CASES = [c if len(c) == 9 else c + ("",) for c in CASES]
 
 
 def run(ctx, oid, obj, rays, enc=False):
@@ -41,14 +44,16 @@ def run(ctx, oid, obj, rays, enc=False):
     return {"hits": out.cpu().numpy(), **{k: v.cpu().numpy() for k, v in bufs.items()}}
 
 
-@pytest.mark.parametrize("feat,mlp,F,levels,width,H,V,density", CASES)
-def test_tile_edges(feat, mlp, F, levels, width, H, V, density):
+@pytest.mark.parametrize("feat,mlp,F,levels,width,H,V,density,aligned", CASES)
+def test_tile_edges(feat, mlp, F, levels, width, H, V, density, aligned):
     import torch
     from tests.test_oracle_pins import tiny_object, adversarial_rays
     torch.cuda.init()
     rng = np.random.default_rng(levels * 7 + H)
     occ = rng.uniform(size=V ** 3) < density
     R = [max(1, int(V * (l + 1) / 3)) for l in range(levels)]
+    if aligned:
+        R = [V * (l + 1) + (0 if aligned == "all" or l % 2 == 0 else 1) for l in range(levels)]
     obj = tiny_object(V, occ, H=H, L=levels, F=F, R=R, log2_T=9, width=width, n_hidden=2, seed=levels)
     obj.tables *= np.float32(1e-2)
     base = adversarial_rays(rng, V, n_random=400).astype(np.float32)
