@@ -503,7 +503,7 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
 }
 
 template <typename TF, typename TM, int F, int WIDTH, bool PAIRS, int R>
-__global__ __launch_bounds__(kBlock) void k_query(QueryArgs A, uint32_t lds_bytes)
+__global__ __launch_bounds__(kBlock, 4) void k_query(QueryArgs A, uint32_t lds_bytes)
 {
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];
     __shared__ QueryShared<R> S;
