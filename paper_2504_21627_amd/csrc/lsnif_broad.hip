@@ -35,10 +35,10 @@ lsnif_status count_pairs(lsnif_ctx *ctx, uint32_t n_objs, const lsnif_ray *d_ray
                          uint32_t &total)
 {
     const size_t n1 = (size_t)n_rays + 1, parts = (n1 + 1023) / 1024;
-    const uint32_t words = (n_inst + 31) / 32;
-    const uint32_t mask_words = words <= kBroadMaskWords ? words : 0u;
-    lsnif_status st = grow_workspace(ctx->bws, ctx->bws_bytes,
-                                     al256(n1 * 4) + al256(parts * 4) + al256((size_t)mask_words * n_rays * 4));
+    const bool masks = n_inst <= kBroadMaskInst;
+    // a byte of bits per ray and 8 instances, in whole 32-bit words per ray
+    const size_t mask_bytes = masks ? (size_t)((n_inst + 31) / 32) * n_rays * 4 : 0;
+    lsnif_status st = grow_workspace(ctx->bws, ctx->bws_bytes, al256(n1 * 4) + al256(parts * 4) + al256(mask_bytes));
     if (st) return st;
     B = BroadArgs{};
     B.rays = reinterpret_cast<const float4 *>(d_rays);
@@ -48,11 +48,9 @@ lsnif_status count_pairs(lsnif_ctx *ctx, uint32_t n_objs, const lsnif_ray *d_ray
     B.objs = static_cast<const ObjDev *>(ctx->d_table);
     B.n_objs = n_objs;
     B.offsets = static_cast<uint32_t *>(ctx->bws);
-    uint32_t *part = reinterpret_cast<uint32_t *>(static_cast<char *>(ctx->bws) + al256(n1 * 4));
-    B.mask_words = mask_words;
-    B.masks = reinterpret_cast<uint32_t *>(static_cast<char *>(ctx->bws) + al256(n1 * 4) + al256(parts * 4));
+    B.part = reinterpret_cast<uint32_t *>(static_cast<char *>(ctx->bws) + al256(n1 * 4));
+    if (masks) B.masks = static_cast<uint8_t *>(ctx->bws) + al256(n1 * 4) + al256(parts * 4);
     HIP_TRY(launch_broad_count(B, s));
-    HIP_TRY(launch_exclusive_scan(B.offsets, (uint32_t)n1, part, s));
     HIP_TRY(hipMemcpyAsync(&total, B.offsets + n_rays, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     return LSNIF_OK;

@@ -834,13 +834,13 @@ struct BroadArgs {
     uint32_t n_objs;
     uint32_t *offsets;        // [n_rays + 1]: pairs per ray, then their exclusive scan
     uint32_t *pair_ray, *pair_inst;
-    // With mask_words > 0 the counting pass also records which instances each ray
-    // meets (bit i % 32 of word i / 32, word-major: masks[(i / 32) n_rays + r]) and
-    // the writing pass lists the pairs from those bits instead of testing again.
-    uint32_t *masks;
-    uint32_t mask_words;
+    // With at most kBroadMaskInst instances a first pass records which of them each ray meets,
+    // a byte for every 8 (bit i % 8 of masks[(i / 8) n_rays + r]); the counting and the
+    // writing pass read those bytes.
+    uint8_t *masks;           // NULL: more instances
+    uint32_t *part;           // partial sums of the scan of the counts
 };
-constexpr uint32_t kBroadMaskWords = 8;   // instance masks for launches of at most 256 instances
+constexpr uint32_t kBroadMaskInst = 256;
 
 // ------------------------------------------------------------ merged serving
 // One member of a merged serving launch: its own buffers and where its rays and

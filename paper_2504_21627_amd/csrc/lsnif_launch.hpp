@@ -28,6 +28,10 @@ __host__ __device__ inline size_t radix_hist_words(uint32_t n)
     return counters + (counters + 1023u) / 1024u;
 }
 __host__ __device__ inline size_t radix_ws_words(uint32_t n) { return 4u * (size_t)n + radix_hist_words(n); }
+// Up to kGroupMax items, keys of at most 20 bits are put in order in two passes of 10-bit
+// digits whose blocks read the counters of all blocks (block-major, `digits` per block)
+// and sum them themselves: no launches for the scans.
+constexpr uint32_t kGroupMax = 1u << 18, kGroupDigits = 1024, kGroupBits = 10;
 struct Geom;
 struct QueryArgs;
 struct DebugArgs;
@@ -43,8 +47,8 @@ hipError_t launch_walk(const QueryArgs &A, bool pairs, bool recheck, uint32_t ma
 hipError_t launch_debug(const DebugArgs &D, hipStream_t s);
 // Gather ceiling: the query's gathers alone, each ray's feature sum into sums[r].
 hipError_t launch_gather_only(const QueryArgs &A, int feat_dtype, int F, float *sums, uint32_t grid, hipStream_t s);
-// Broad phase: pairs per ray into B.offsets (and 0 at offsets[n_rays]), then, after an
-// exclusive scan of the n_rays + 1 counters, the pairs themselves.
+// Broad phase: the exclusive scan of the pairs per ray into B.offsets (their total at
+// offsets[n_rays]), then the pairs themselves.
 struct BroadArgs;
 hipError_t launch_broad_count(const BroadArgs &B, hipStream_t s);
 hipError_t launch_broad_write(const BroadArgs &B, hipStream_t s);
@@ -53,8 +57,9 @@ hipError_t launch_broad_write(const BroadArgs &B, hipStream_t s);
 struct BounceArgs;
 hipError_t launch_bounce_mark(const BounceArgs &B, hipStream_t s);
 hipError_t launch_bounce_write(const BounceArgs &B, hipStream_t s);
-// In-place exclusive scan of n counters; `part` holds (n + 1023) / 1024 partial sums.
-hipError_t launch_exclusive_scan(uint32_t *v, uint32_t n, uint32_t *part, hipStream_t s);
+// In-place exclusive scan of n counters; `part` holds (n + 1023) / 1024 partial sums, with
+// `summed` the sums of each 1,024 counters already.
+hipError_t launch_exclusive_scan(uint32_t *v, uint32_t n, uint32_t *part, hipStream_t s, bool summed = false);
 // Merged serving launches: stage the members' rays and re-indexed pairs, and copy the
 // staged answers back to each member's output.
 struct MergeArgs;
@@ -69,6 +74,9 @@ hipError_t launch_pairs_payload(const PairPlan &P, hipStream_t s);
 // partial sums of their scan; counted: they already hold this pass's per-block counts.
 hipError_t launch_radix_pass(const uint32_t *sk, const uint32_t *sv, uint32_t *dk, uint32_t *dv, uint32_t n,
                              uint32_t *hist, uint32_t shift, bool counted, hipStream_t s);
+// The counts of the digit (key >> shift, below `digits`) of each block's items, block-major.
+hipError_t launch_digit_count(const uint32_t *sk, uint32_t n, uint32_t *hist, uint32_t shift, uint32_t digits,
+                              hipStream_t s);
 // Sorts rays 0..n-1 by coherence key in `ws` (radix_ws_words(n) words);
 // *order receives the sorted ray indices (inside ws).
 hipError_t launch_coherence_sort(const Geom &g, const float4 *rays, uint32_t n, uint32_t *ws, uint32_t **order,
