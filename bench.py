@@ -618,13 +618,13 @@ def bench_t1(L, steps, warmup, data, cpu=True, quality_steps=400):
             torch.cuda.synchronize()
             ms = e0.elapsed_time(e1) / steps
             flops = train_flops_per_ray(obj) * n
-            # the same steps again with the library's phase events: layer products and scatter
+            # the same steps again with the library's events around the step's kernel
             L.lsnif_profile_enable(ctx, True)
             for _ in range(steps):
                 L.lsnif_train_step(tr, rays, tgt, loss)
-            prod_ms, scat_ms, k = L.lsnif_train_profile_read(tr)
+            prod_ms, _, k = L.lsnif_train_profile_read(tr)
             L.lsnif_profile_enable(ctx, False)
-            prod_ms, scat_ms = prod_ms / k, scat_ms / k
+            prod_ms /= k
             cnt = torch.empty(n, dtype=torch.int32, device="cuda")
             tmp = torch.empty((n, 6), dtype=torch.float32, device="cuda")
             L.lsnif_query_debug(ctx, oid, rays, tmp, {"count": cnt})
@@ -637,20 +637,16 @@ def bench_t1(L, steps, warmup, data, cpu=True, quality_steps=400):
                         "layer_tflops": flops / ms / 1e9, "loss_step1": loss_first,
                         "loss_last": float(loss.item()), "adam_steps": 2 * steps + warmup + 1,
                         "roofline": {
-                            "products": {"bound": "mfma", "achieved": flops / prod_ms / 1e9,
-                                         "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                                         "frac": flops / prod_ms / 1e9 / MFMA_FP32_PEAK_TFLOPS,
-                                         "ms_per_step": prod_ms, "flop_per_step": flops,
-                                         "what": "forward and backward layer products (fp32 matrix cores), "
-                                                 "with the weight-gradient partial sums"},
-                            "scatter": {"bound": "hbm", "achieved": scat_bytes / scat_ms / 1e6,
-                                        "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                                        "frac": scat_bytes / scat_ms / 1e6 / HBM_PEAK_GBS,
-                                        "ms_per_step": scat_ms, "bytes_per_step": scat_bytes,
-                                        "points_per_step": points,
-                                        "what": "k_train_enc<true>: per boundary point, read its L x F encoding "
-                                                "gradients and add F floats to each of its corners "
-                                                "(4 on face-aligned levels, 8 elsewhere)"}}})
+                            "step_kernel": {"bound": "mfma", "achieved": flops / prod_ms / 1e9,
+                                            "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
+                                            "frac": flops / prod_ms / 1e9 / MFMA_FP32_PEAK_TFLOPS,
+                                            "ms_per_step": prod_ms, "flop_per_step": flops,
+                                            "scatter_bytes_per_step": scat_bytes, "points_per_step": points,
+                                            "what": "k_train_fused and the weight-gradient partial sums: encoding, "
+                                                    "forward and backward layer products (fp32 matrix cores; rays "
+                                                    "without voxels and unused inputs are counted but not "
+                                                    "multiplied), losses, and F floats added to each corner of a "
+                                                    "boundary point (4 on face-aligned levels, 8 elsewhere)"}}})
             if quality_steps:
                 print("[bench] t1: training on to score held-out rays", file=sys.stderr, flush=True)
                 res["trained"] = t1_quality(L, ctx, oid, tr, obj, [(rays_np, tg)] + list(more), test, quality_steps)

@@ -271,6 +271,14 @@ hipError_t launch_radix_pass(const uint32_t *sk, const uint32_t *sv, uint32_t *d
     return hipGetLastError();
 }
 
+hipError_t launch_group_scatter(const uint32_t *sk, const uint32_t *sv, uint32_t *dk, uint32_t *dv, uint32_t n,
+                                const uint32_t *hist, uint32_t digits, uint32_t shift, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_group_scatter, dim3((n + kRadixTile - 1) / kRadixTile), dim3(kBlock), 0, s, sk, sv, dk, dv, n,
+                       hist, digits, shift);
+    return hipGetLastError();
+}
+
 hipError_t launch_coherence_sort(const Geom &g, const float4 *rays, uint32_t n, uint32_t *ws, uint32_t **order,
                                  hipStream_t s)
 {

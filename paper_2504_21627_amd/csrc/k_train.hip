@@ -11,8 +11,9 @@
 
 namespace lsnif {
 
-__global__ __launch_bounds__(kBlock) void k_train_fill(float *a, uint64_t na, float *b, uint64_t nb)
+__global__ __launch_bounds__(kBlock) void k_train_fill(float *a, uint64_t na, float *b, uint64_t nb, uint32_t *live)
 {
+    if (live && blockIdx.x == 0 && threadIdx.x == 0) *live = 0u;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < na + nb; i += stride) {
         if (i < na) a[i] = 0.0f;
@@ -269,8 +270,6 @@ __global__ __launch_bounds__(kBlock) void k_sum_copies(float *a, uint64_t n, uin
     }
 }
 
-__device__ __forceinline__ float sigmoidf(float z) { return 1.0f / (1.0f + expf(-z)); }
-
 // Thread = ray: its loss and d loss / d z.  The block's rays' losses are summed
 // in float32 (waves, then the block) into loss_part[block]; k_train_loss_final
 // adds the blocks' sums in a fixed order, so the batch loss is deterministic.
@@ -290,47 +289,7 @@ __global__ __launch_bounds__(kBlock) void k_train_loss(TrainLossArgs A)
             setup_ray(A.g, A.rays[2 * r], A.rays[2 * r + 1], w);
             const lsnif_train_target y = A.gt[r];
             const float inv_n = 1.0f / (float)A.n;
-            const float yh = y.hit ? 1.0f : 0.0f;
-            // occlusion: softplus(z0) - y z0, the stable form
-            const float z0 = z[0];
-            float l = (fmaxf(z0, 0.0f) + log1pf(expf(-fabsf(z0)))) - yh * z0;
-            d[0] = sigmoidf(z0) - yh;
-            if (y.hit) {
-                // local hit distance
-                float tau = (y.t - w.ta) / (w.tb - w.ta);
-                tau = fminf(fmaxf(tau, 0.0f), 1.0f);
-                const float s1 = sigmoidf(z[1]), e1 = s1 - tau;
-                l += fabsf(e1);
-                d[1] = (e1 > 0.0f ? 1.0f : (e1 < 0.0f ? -1.0f : 0.0f)) * (s1 * (1.0f - s1));
-                // normal: 1 - cosine similarity
-                const float nn = sqrtf((z[2] * z[2] + z[3] * z[3]) + z[4] * z[4]);
-                const float dot = (z[2] * y.n[0] + z[3] * y.n[1]) + z[4] * y.n[2];
-                const float den = fmaxf(nn, 1e-8f);
-                const float cs = dot / den;
-                l += 1.0f - cs;
-                for (int b = 0; b < 3; ++b)
-                    d[2 + b] = nn > 1e-8f ? -(y.n[b] / nn - cs * (z[2 + b] / nn) / nn) : -(y.n[b] / 1e-8f);
-                uint32_t m0 = 5;
-                if (A.has_albedo) {
-                    for (int c = 0; c < 3; ++c) {
-                        const float a = sigmoidf(z[5 + c]), e = a - y.albedo[c];
-                        const float q = (a + 0.01f) * (a + 0.01f);
-                        l += (e * e / q) / 3.0f;
-                        d[5 + c] = ((2.0f * e / q) / 3.0f) * (a * (1.0f - a));
-                    }
-                    m0 = 8;
-                }
-                if (y.material >= 0 && (uint32_t)y.material < A.n_mat) {
-                    float mx = z[m0];
-                    for (uint32_t k = 1; k < A.n_mat; ++k) mx = fmaxf(mx, z[m0 + k]);
-                    float sum = 0.0f;
-                    for (uint32_t k = 0; k < A.n_mat; ++k) sum += expf(z[m0 + k] - mx);
-                    l += (mx + logf(sum)) - z[m0 + y.material];
-                    for (uint32_t k = 0; k < A.n_mat; ++k)
-                        d[m0 + k] = expf(z[m0 + k] - mx) / sum - ((int32_t)k == y.material ? 1.0f : 0.0f);
-                }
-            }
-            lsum = l;
+            lsum = ray_loss(A, y, w.ta, w.tb, z, d);
 #pragma unroll
             for (int k = 0; k < kMaxOut; ++k) d[k] *= inv_n;
         }
@@ -381,9 +340,9 @@ static uint32_t stream_blocks(uint64_t count)
     return (uint32_t)(b < 8192 ? (b ? b : 1) : 8192);
 }
 
-hipError_t launch_train_fill(float *a, uint64_t na, float *b, uint64_t nb, hipStream_t s)
+hipError_t launch_train_fill(float *a, uint64_t na, float *b, uint64_t nb, uint32_t *live, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_train_fill, dim3(stream_blocks(na + nb)), dim3(kBlock), 0, s, a, na, b, nb);
+    hipLaunchKernelGGL(k_train_fill, dim3(stream_blocks(na + nb)), dim3(kBlock), 0, s, a, na, b, nb, live);
     return hipGetLastError();
 }
 
@@ -432,9 +391,8 @@ hipError_t launch_train_loss(const TrainLossArgs &A, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_train_loss_final(const float *part, uint32_t n, float *loss, hipStream_t s)
+hipError_t launch_train_loss_final(const float *part, uint32_t nparts, uint32_t n, float *loss, hipStream_t s)
 {
-    const uint32_t nparts = (n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_train_loss_final, dim3(1), dim3(kBlock), 0, s, part, nparts, n, loss);
     return hipGetLastError();
 }

@@ -77,6 +77,9 @@ hipError_t launch_radix_pass(const uint32_t *sk, const uint32_t *sv, uint32_t *d
 // The counts of the digit (key >> shift, below `digits`) of each block's items, block-major.
 hipError_t launch_digit_count(const uint32_t *sk, uint32_t n, uint32_t *hist, uint32_t shift, uint32_t digits,
                               hipStream_t s);
+// One grouping pass of at most kGroupMax items by such a digit, with those counts.
+hipError_t launch_group_scatter(const uint32_t *sk, const uint32_t *sv, uint32_t *dk, uint32_t *dv, uint32_t n,
+                                const uint32_t *hist, uint32_t digits, uint32_t shift, hipStream_t s);
 // Sorts rays 0..n-1 by coherence key in `ws` (radix_ws_words(n) words);
 // *order receives the sorted ray indices (inside ws).
 hipError_t launch_coherence_sort(const Geom &g, const float4 *rays, uint32_t n, uint32_t *ws, uint32_t **order,

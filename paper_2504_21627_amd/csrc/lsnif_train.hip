@@ -45,7 +45,8 @@ struct lsnif_trainer {
     void *ws = nullptr;
     size_t ws_bytes = 0;
     // with the context's profiling on: per step, events around the forward layer products,
-    // the backward layer products (with their partial sums) and the table-gradient scatter
+    // the backward layer products (with their partial sums) and the table-gradient scatter; where
+    // one kernel is the step: around it, around the partial sums, and the last two NULL
     std::vector<std::array<hipEvent_t, 6>> prof;
     std::vector<hipEvent_t> spare;
 };
@@ -88,7 +89,34 @@ struct StepWs {
     float *z, *dz;    // [n][out_dim]
     float *part;      // partial weight-gradient products
     float *loss_part; // per-block loss sums
+    uint32_t *sort;   // the fused step's ray order (order_ws_words(n) words), then the number of its rows
 };
+
+// Blocks of 32 x 32 of layer k's weight gradient.
+uint32_t grad_blocks(const Object &ob, int k)
+{
+    const uint32_t mb = (uint32_t)ob.width / 32u, in0 = (uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F);
+    return (k ? mb : (in0 + 31u) / 32u) * (k == ob.mlp.n_hidden ? 1u : mb);
+}
+
+// Whether one kernel holds a step of the object: its weight gradients in 12 accumulator blocks
+// per wave, its activations in LDS.
+bool fused(const Object &ob)
+{
+    uint32_t blocks = 0;
+    for (int k = 0; k <= ob.mlp.n_hidden; ++k) blocks += grad_blocks(ob, k);
+    const uint32_t in0 = (uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F);
+    return blocks <= 48u && 4u * (uint32_t)ob.geom.H <= (uint32_t)(ob.mlp.n_hidden * (ob.width + 4)) &&
+           step_lds_bytes(in0, (uint32_t)ob.mlp.n_hidden, (uint32_t)ob.width) <= (150u << 10);
+}
+
+// Floats of the transposed weights: layer 0's rows padded to 32 j.
+uint32_t trans_row(const Object &ob) { return ((uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F) + 31u) / 32u * 32u; }
+size_t trans_floats(const Object &ob)
+{
+    const size_t in0 = (size_t)ob.geom.H * ob.geom.L * ob.geom.F;
+    return weight_floats(ob) + (trans_row(ob) - in0) * ob.width;
+}
 
 constexpr uint32_t kCopyBudget = 1u << 30;   // bytes for the table-gradient copies
 
@@ -106,6 +134,7 @@ uint32_t wgrad_chunk(uint32_t M, uint32_t N, uint32_t n)
 // scratch of their two-pass sum.
 size_t part_floats(const Object &ob, uint32_t n)
 {
+    if (fused(ob)) return ((size_t)step_blocks(n) + kSumGroups) * weight_floats(ob) + trans_floats(ob);
     const uint32_t in0 = (uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F), Wd = (uint32_t)ob.width;
     size_t best = 0;
     for (int k = 0; k <= ob.mlp.n_hidden; ++k) {
@@ -119,9 +148,10 @@ size_t part_floats(const Object &ob, uint32_t n)
 size_t step_ws_bytes(const Object &ob, uint32_t n)
 {
     const size_t in = (size_t)ob.geom.H * ob.geom.L * ob.geom.F, od = (size_t)ob.mlp.out_dim;
-    return al256((size_t)n * (ob.geom.H / 2) * 4) + al256(n) + al256((size_t)n * in * 4) +
-           (size_t)ob.mlp.n_hidden * al256((size_t)n * ob.width * 4) + 2 * al256((size_t)n * od * 4) +
-           al256(part_floats(ob, n) * 4) + al256((size_t)(n + kBlock - 1) / kBlock * 4);
+    const size_t acts = fused(ob) ? 0 : al256((size_t)n * in * 4) + (size_t)ob.mlp.n_hidden * al256((size_t)n * ob.width * 4);
+    const size_t outs = fused(ob) ? al256((order_ws_words(n) + 1) * 4) : 2 * al256((size_t)n * od * 4);
+    return al256((size_t)n * (ob.geom.H / 2) * 4) + al256(n) + acts + outs +
+           al256(part_floats(ob, n) * 4) + al256(((size_t)n + kStepRows - 1) / kStepRows * 4);
 }
 
 StepWs carve(const Object &ob, uint32_t n, void *ws)
@@ -133,16 +163,21 @@ StepWs carve(const Object &ob, uint32_t n, void *ws)
     w += al256((size_t)n * (ob.geom.H / 2) * 4);
     S.nvox = reinterpret_cast<uint8_t *>(w);
     w += al256(n);
-    S.x0 = reinterpret_cast<float *>(w);
-    w += al256((size_t)n * in * 4);
-    for (int k = 1; k <= ob.mlp.n_hidden; ++k) {
-        S.act[k] = reinterpret_cast<float *>(w);
-        w += al256((size_t)n * ob.width * 4);
+    if (fused(ob)) {
+        S.sort = reinterpret_cast<uint32_t *>(w);
+        w += al256((order_ws_words(n) + 1) * 4);
+    } else {
+        S.x0 = reinterpret_cast<float *>(w);
+        w += al256((size_t)n * in * 4);
+        for (int k = 1; k <= ob.mlp.n_hidden; ++k) {
+            S.act[k] = reinterpret_cast<float *>(w);
+            w += al256((size_t)n * ob.width * 4);
+        }
+        S.z = reinterpret_cast<float *>(w);
+        w += al256((size_t)n * od * 4);
+        S.dz = reinterpret_cast<float *>(w);
+        w += al256((size_t)n * od * 4);
     }
-    S.z = reinterpret_cast<float *>(w);
-    w += al256((size_t)n * od * 4);
-    S.dz = reinterpret_cast<float *>(w);
-    w += al256((size_t)n * od * 4);
     S.part = reinterpret_cast<float *>(w);
     w += al256(part_floats(ob, n) * 4);
     S.loss_part = reinterpret_cast<float *>(w);
@@ -167,7 +202,9 @@ lsnif_status grads(lsnif_trainer *tr, const Object &ob, const lsnif_ray *d_rays,
     float *tab = static_cast<float *>(ob.d_tab);
     float *W = static_cast<float *>(const_cast<void *>(ob.d_w));
     float *gtab = tr->grad, *gW = tr->grad + tr->copies * tr->n_tab;
-    HIP_TRY(launch_train_fill(gtab, tr->copies * tr->n_tab, gW, tr->n_w, s));
+    const bool one = fused(ob);
+    uint32_t *n_live = one ? S.sort + order_ws_words(n) : nullptr;
+    HIP_TRY(launch_train_fill(gtab, tr->copies * tr->n_tab, gW, tr->n_w, n_live, s));
     // voxel lists: the query path's walk, rays in their given order
     QueryArgs A{};
     A.g = ob.geom;
@@ -187,8 +224,63 @@ lsnif_status grads(lsnif_trainer *tr, const Object &ob, const lsnif_ray *d_rays,
     E.replicas = tr->copies;
     E.n_tab = tr->n_tab;
     E.x = S.x0;
-    HIP_TRY(launch_train_encode(E, false, s));
     const float slope = mlp.act == LSNIF_LEAKY_RELU ? mlp.slope : 0.0f;
+    TrainLossArgs Lo{};
+    Lo.g = ob.geom;
+    Lo.rays = A.rays;
+    Lo.gt = d_gt;
+    Lo.n = n;
+    Lo.nvox = S.nvox;
+    Lo.z = S.z;
+    Lo.dz = S.dz;
+    Lo.ldz = od;
+    Lo.out_dim = od;
+    Lo.n_mat = (uint32_t)mlp.n_mat;
+    Lo.has_albedo = (uint32_t)mlp.has_albedo;
+    Lo.loss_part = S.loss_part;
+    uint32_t nparts = (n + kBlock - 1) / kBlock;
+    if (one) {
+        uint32_t *order = nullptr;
+        HIP_TRY(launch_train_order(S.nvox, n, (uint32_t)ob.geom.H / 2u, S.sort, &order, n_live, s));
+        TrainStepArgs T{};
+        T.L = Lo;
+        T.lists = S.lists;
+        T.order = order;
+        T.n_live = n_live;
+        T.tab = tab;
+        T.W = W;
+        for (int k = 0; k < 8; ++k) T.off[k] = mlp.off[k];
+        T.WT = S.part;
+        T.ldT0 = trans_row(ob);
+        for (uint32_t k = 0; k < nh; ++k) T.offT[k + 1] = T.offT[k] + (k ? Wd : T.ldT0) * Wd;
+        T.n_hidden = nh;
+        T.slope = slope;
+        T.gtab = gtab;
+        T.replicas = tr->copies;
+        T.n_tab = tr->n_tab;
+        for (uint32_t k = 0; k <= nh; ++k) T.first[k + 1] = T.first[k] + grad_blocks(ob, (int)k);
+        T.part = S.part + trans_floats(ob);
+        T.n_w = (uint32_t)tr->n_w;
+        T.loss_part = S.loss_part;
+        nparts = step_blocks(n);
+        HIP_TRY(mark(0));
+        HIP_TRY(launch_train_step(T, (uint32_t)ob.F, Wd, s));
+        HIP_TRY(mark(1));
+        HIP_TRY(mark(2));
+        HIP_TRY(launch_sum_partials(T.part, nparts, 1u, T.n_w, T.part + (size_t)nparts * T.n_w, gW, T.n_w, s));
+        HIP_TRY(mark(3));
+        if (ev[0]) {   // the scatter is part of the step's kernel
+            for (int i = 4; i < 6; ++i) {
+                tr->spare.push_back(ev[i]);
+                ev[i] = nullptr;
+            }
+            tr->prof.push_back(ev);
+        }
+        HIP_TRY(launch_sum_copies(gtab, tr->n_tab, tr->copies, s));
+        if (d_loss) HIP_TRY(launch_train_loss_final(S.loss_part, nparts, n, d_loss, s));
+        return LSNIF_OK;
+    }
+    HIP_TRY(launch_train_encode(E, false, s));
     auto layer_in = [&](uint32_t k) { return k == 0 ? S.x0 : S.act[k]; };
     auto in_dim = [&](uint32_t k) { return k == 0 ? in0 : Wd; };
     auto out_dim = [&](uint32_t k) { return k == nh ? od : Wd; };
@@ -213,19 +305,6 @@ lsnif_status grads(lsnif_trainer *tr, const Object &ob, const lsnif_ray *d_rays,
         HIP_TRY(launch_train_gemm(G, k == nh ? kEpiStore : kEpiAct, s));
     }
     HIP_TRY(mark(1));
-    TrainLossArgs Lo{};
-    Lo.g = ob.geom;
-    Lo.rays = A.rays;
-    Lo.gt = d_gt;
-    Lo.n = n;
-    Lo.nvox = S.nvox;
-    Lo.z = S.z;
-    Lo.dz = S.dz;
-    Lo.ldz = od;
-    Lo.out_dim = od;
-    Lo.n_mat = (uint32_t)mlp.n_mat;
-    Lo.has_albedo = (uint32_t)mlp.has_albedo;
-    Lo.loss_part = S.loss_part;
     HIP_TRY(launch_train_loss(Lo, s));
     // backward: g holds d loss / d (output of layer k)
     const float *g = S.dz;
@@ -274,7 +353,7 @@ lsnif_status grads(lsnif_trainer *tr, const Object &ob, const lsnif_ray *d_rays,
     HIP_TRY(mark(5));
     if (ev[0]) tr->prof.push_back(ev);
     HIP_TRY(launch_sum_copies(gtab, tr->n_tab, tr->copies, s));
-    if (d_loss) HIP_TRY(launch_train_loss_final(S.loss_part, n, d_loss, s));
+    if (d_loss) HIP_TRY(launch_train_loss_final(S.loss_part, nparts, n, d_loss, s));
     return LSNIF_OK;
 }
 
@@ -372,7 +451,8 @@ void lsnif_trainer_destroy(lsnif_trainer *tr)
     (void)hipFree(tr->v);
     (void)hipFree(tr->ws);
     for (auto &v : tr->prof)
-        for (hipEvent_t e : v) (void)hipEventDestroy(e);
+        for (hipEvent_t e : v)
+            if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : tr->spare) (void)hipEventDestroy(e);
     delete tr;
 }
@@ -425,13 +505,15 @@ lsnif_status lsnif_train_profile_read(lsnif_trainer *tr, double *products_ms, do
     lsnif_status st = LSNIF_OK;
     for (auto &v : tr->prof) {
         float a = 0.0f, b = 0.0f, c = 0.0f;
-        if (!st && (hipEventSynchronize(v[5]) != hipSuccess || hipEventElapsedTime(&a, v[0], v[1]) != hipSuccess ||
+        if (!st && (hipEventSynchronize(v[5] ? v[5] : v[3]) != hipSuccess ||
+                    hipEventElapsedTime(&a, v[0], v[1]) != hipSuccess ||
                     hipEventElapsedTime(&b, v[2], v[3]) != hipSuccess ||
-                    hipEventElapsedTime(&c, v[4], v[5]) != hipSuccess))
+                    (v[5] && hipEventElapsedTime(&c, v[4], v[5]) != hipSuccess)))
             st = fail(LSNIF_E_DEVICE, "reading the training step's events failed");
         prod += (double)a + (double)b;
         scat += c;
-        for (hipEvent_t e : v) tr->spare.push_back(e);
+        for (hipEvent_t e : v)
+            if (e) tr->spare.push_back(e);
     }
     if (steps) *steps = (uint32_t)tr->prof.size();
     tr->prof.clear();
