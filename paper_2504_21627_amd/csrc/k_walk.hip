@@ -6,11 +6,10 @@ namespace lsnif {
 
 // The walk with G lanes per ray (find_voxels), then the first H / 2 voxels found, in
 // order of their place.  A wave's serial walk is one dependent chain of up to 3V
-// divergent steps, about 1 us each while few waves share a SIMD, however few the
-// rays; here the chain is a few rounds of crossings.  Walks measured (us, one lane
-// per ray, then this): 256 rays at V = 128 138 and 13, 4,096 at V = 32 70 and 16,
-// 32,000 at V = 128 148 and 48, 2,500 pairs at V up to 256 220 and 23, 262,144 pairs
-// 263 and 173.
+// divergent steps, 0.3 us and more each while few waves share a SIMD, however few
+// the rays; here the chain is a few rounds of crossings.  Walks measured (us, one
+// lane per ray, then this): 4,096 rays at V = 32 40 and 16, 32,000 at V = 128 66
+// and 48, 2,500 pairs at V up to 256 105 and 23.
 constexpr uint32_t kFoundRoom = 63;   // voxels of a ray kept; with more, one lane walks it
 
 // Orders the LDS accesses of a wave's lanes (a ray's lanes are in one wave).
@@ -66,33 +65,32 @@ __global__ __launch_bounds__(kBlock) void k_walk_wide(QueryArgs A)
     }
 }
 
-// By the launch's slots n and its largest grid V.  64 lanes per ray and a plane per
-// lane up to 8,192 slots (4,096 rays: 16 us at V = 32, 19 at 128; 8 lanes and bricks:
-// 26 and 43; 16,000 rays at V = 128: 48 and 40), 8 lanes and a brick boundary per lane up
-// to 65,536 + 1,024 V, one lane beyond: its work is half, and its chain (65 us at V = 32,
-// 140 at 128, 250 at 256) matters less the longer the launch (V = 32: 40,000 slots 67 us
-// with one lane and 36 with 8, 160,000 80 and 102; V = 128: 128,000 147 and 91, 512,000 191
-// and 290).
+// By the launch's slots n.  64 lanes per ray and a plane per lane up to 8,192 slots (4,096 rays:
+// 16 us at V = 32, 19 at 128; 8 lanes and bricks: 24 and 42; 16,000 rays at V = 128: 48 and
+// 40), 8 lanes and a brick boundary per lane up to 57,344, one lane beyond: its chain (40 us at
+// V = 32, 66 at 128, 105 at 256) takes as long for few rays as for a chip full (us, 8 lanes and
+// one: V = 32, 40,000 slots 36 and 38, 80,000 59 and 41; V = 128, 64,000 62 and 66, 128,000 93 and
+// 68; pairs at V up to 256, 24,000 78 and 103, 154,000 170 and 112).
 template <bool PAIRS, bool RECHECK>
-static void go(const QueryArgs &A, uint32_t max_V, uint32_t grid, hipStream_t s)
+static void go(const QueryArgs &A, uint32_t grid, hipStream_t s)
 {
     const uint32_t n = grid * kBlock;
     if (n <= 8192u)
         hipLaunchKernelGGL((k_walk_wide<PAIRS, RECHECK, 64, true>), dim3(grid * 64u), dim3(kBlock), 0, s, A);
-    else if (n <= 65536u + 1024u * max_V)
+    else if (n <= 57344u)
         hipLaunchKernelGGL((k_walk_wide<PAIRS, RECHECK, 8, false>), dim3(grid * 8u), dim3(kBlock), 0, s, A);
     else
         hipLaunchKernelGGL((k_walk<PAIRS, RECHECK>), dim3(grid), dim3(kBlock), 0, s, A);
 }
 
-hipError_t launch_walk(const QueryArgs &A, bool pairs, bool recheck, uint32_t max_V, uint32_t grid, hipStream_t s)
+hipError_t launch_walk(const QueryArgs &A, bool pairs, bool recheck, uint32_t grid, hipStream_t s)
 {
     if (pairs) {
-        if (recheck) go<true, true>(A, max_V, grid, s);
-        else go<true, false>(A, max_V, grid, s);
+        if (recheck) go<true, true>(A, grid, s);
+        else go<true, false>(A, grid, s);
     } else {
-        if (recheck) go<false, true>(A, max_V, grid, s);
-        else go<false, false>(A, max_V, grid, s);
+        if (recheck) go<false, true>(A, grid, s);
+        else go<false, false>(A, grid, s);
     }
     return hipGetLastError();
 }

@@ -225,116 +225,128 @@ __device__ __forceinline__ bool keep_f64(const VRay &w, const int c[3], int V)
     return __builtin_fmin(tout, tb) > __builtin_fmax(tin, ta);
 }
 
+// The next float above a finite x.
+__device__ __forceinline__ float next_up(float x)
+{
+    const int b = (int)__float_as_uint(x);
+    return b == (int)0x80000000 ? __uint_as_float(1u) : __uint_as_float((uint32_t)(b >= 0 ? b + 1 : b - 1));
+}
+
 // The voxel walk.  Emits, in order along the ray, the packed coordinates of
 // the first `cap` occupied voxels whose [entry, exit] overlaps [ta, tb] with
 // positive length; list[j * stride] receives voxel j.  Steps the axis of the
 // earliest exit, the lowest axis on ties.  Occupancy is read a brick at a
 // time: the coarse bit (from `coarse`, LDS or global) and, for a non-empty
 // brick, its 64-bit mask, loaded once on entering the brick.  An empty brick
-// is crossed in one step that lands on the cell the cell-by-cell walk reaches
-// next; every decision still compares values of the same plane functions.
+// is crossed in one step; every decision still compares values of the same
+// plane functions.
+//
+// The lanes of a wave are in bricks and cells of their own, so a wave pays for every path that
+// some lane takes.  Both steps are therefore the same few instructions (the earliest of three
+// planes, then that axis's next one, a cell or a brick further), and the cell at which a brick
+// is entered is found only for bricks that hold voxels, without branches: the planes of each
+// axis that come before the entry are counted.  One lane per ray (us; finding the entry cell
+// of every brick with loops, then this): 1,048,576 rays at V = 32 237 and 157, 2,097,152 at
+// V = 128 447 and 233, 262,144 152 and 72, 1,000,003 diffuse ones 231 and 104.  Waiting until
+// 2, 4 or 16 lanes have a brick to enter: 241, 270 and 311 for 233.
 template <bool RECHECK>
 __device__ __forceinline__ int walk_voxels(const Geom &g, const VRay &w, const uint32_t *coarse,
                                            uint32_t *list, uint32_t stride, int cap)
 {
     if (!w.cand) return 0;
-    int c[3], st[3], pk[3];
-    float en[3], ex[3];
+    const int V = g.V;
+    // Per axis: cell step (0 on a still axis, whose planes lie at infinity), next plane, where the
+    // brick ends; ex: the next plane's t.
+    float st[3], kp[3], bx[3], ex[3], o[3], iv[3];
+    int sb[3], sl[3];   // steps of the brick's index and of the cell's bit in the brick
+    int brick = 0;
+    float tin = -__builtin_inff(), tb = w.tb;   // tb: no later than the grid's end, also beside an axis of NaN
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        c[a] = start_cell(g, w, a);
-        const bool up = w.d[a] > 0.0f;
-        st[a] = up ? 1 : -1;   // cell step along the ray
-        pk[a] = up ? 1 : 0;    // exit plane of cell k: k + pk
-        if (w.mov & (1u << a)) {
-            cell_span(w, a, c[a], en[a], ex[a]);
-        } else {
-            en[a] = -__builtin_inff();
-            ex[a] = __builtin_inff();
+        const bool mov = w.mov & (1u << a), up = w.d[a] > 0.0f;
+        const int c = start_cell(g, w, a), pitch = a == 0 ? 1 : (a == 1 ? g.NB : g.NB * g.NB);
+        st[a] = mov ? (up ? 1.0f : -1.0f) : 0.0f;
+        o[a] = mov ? w.o[a] : -__builtin_inff();
+        iv[a] = mov ? w.inv[a] : 1.0f;
+        sb[a] = up ? pitch : -pitch;
+        sl[a] = (up ? 1 : -1) * (1 << 2 * a);
+        brick += (c >> 2) * pitch;
+        bx[a] = mov ? (float)((c & ~3) + (up ? 4 : 0)) : (float)(c - 3);   // still: where it would enter at c
+        kp[a] = bx[a];
+        if (mov) {
+            float en, e;
+            cell_span(w, a, c, en, e);
+            tin = fmax2(tin, en);
+            tb = __builtin_fminf(tb, plane_t(up ? (float)V : 0.0f, w.o[a], w.inv[a]));
         }
+        ex[a] = plane_t(kp[a], o[a], iv[a]);
     }
-    int n = 0;
-    const int V = g.V;
-    uint32_t cur = 0xffffffffu;
-    uint64_t mask = 0;
-    for (int it = 0; it < 3 * V; ++it) {
-        const uint32_t b = brick_of(g, c);
-        if (b != cur) {
-            cur = b;
-            mask = ((coarse[b >> 5] >> (b & 31u)) & 1u) ? g.fine[b] : 0ull;
-        }
-        if (mask == 0ull) {
-            // An empty brick lists nothing: go straight to the cell where the cell-by-cell
-            // walk would leave it.  That walk merges the axes' plane crossings in order of
-            // t, ties to the lowest axis, so it leaves along the axis whose brick-boundary
-            // plane comes first in that order, after every other axis has crossed exactly
-            // its in-brick planes that come before it.
-            float T = __builtin_inff();
-            int as = -1;
+    const auto occupied = [&]() { return (coarse[(uint32_t)brick >> 5] >> ((uint32_t)brick & 31u)) & 1u; };
+    bool enter = occupied(), cells = false;   // a brick to enter; in a brick, cell by cell
+    int n = 0, as = 3, bit = 0;
+    float T = w.ta;   // the crossing that led here, along axis `as`
+    uint32_t lo32 = 0, hi32 = 0;
+    for (;;) {   // a plane at a time, all before tb and so inside the grid
+        if (enter) {
+            // The cell-by-cell walk merges the axes' crossings in order of t, ties to the lowest
+            // axis: it enters the brick after every in-brick plane that comes before (T, as) in
+            // that order.
+            const uint64_t mask = g.fine[brick];
+            lo32 = (uint32_t)mask;
+            hi32 = (uint32_t)(mask >> 32);
+            bit = 0;
+            const float after = next_up(T);   // t <= T is t < after
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                if (w.mov & (1u << a)) {
-                    const int lo = c[a] & ~3, hi = lo + 4 < V ? lo + 4 : V;
-                    const float ta = plane_t((float)(w.d[a] > 0.0f ? hi : lo), w.o[a], w.inv[a]);
-                    if (as < 0 || ta < T) { T = ta; as = a; }
-                }
-            }
-            if (T >= w.tb) break;   // the segment ends inside the brick
-            bool out = false;
+                const bool up = st[a] > 0.0f;
+                const float first = up ? bx[a] - 4.0f : bx[a] + 3.0f, Ta = a < as ? after : T;
+                const float p = up ? first + 1.0f : first;   // the entry cell's exit plane
+                float k = 0.0f;
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                if (!(w.mov & (1u << a))) continue;
-                const bool up = w.d[a] > 0.0f;
-                if (a == as) {
-                    const int lo = c[a] & ~3;
-                    c[a] = up ? lo + 4 : lo - 1;
-                    out = c[a] < 0 || c[a] >= V;
-                } else {
-                    for (int s = 0; s < 3; ++s) {
-                        const int nk = up ? c[a] + 1 : c[a] - 1;
-                        if ((nk & ~3) != (c[a] & ~3)) break;
-                        const float t = plane_t((float)(up ? c[a] + 1 : c[a]), w.o[a], w.inv[a]);
-                        if (t < T || (t == T && a < as)) c[a] = nk;
-                        else break;
-                    }
-                }
+                for (int j = 0; j < 3; ++j) k += plane_t(p + (float)j * st[a], o[a], iv[a]) < Ta ? st[a] : 0.0f;
+                kp[a] = p + k;
+                bit |= ((int)(first + k) & 3) << 2 * a;
+                ex[a] = plane_t(kp[a], o[a], iv[a]);
             }
-            if (out) break;
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                if (w.mov & (1u << a)) cell_span(w, a, c[a], en[a], ex[a]);
-            continue;
+            enter = false;
+            cells = true;
         }
-        // A still axis has en = -inf and ex = +inf, so it never decides the interval; the
-        // exit axis is the lowest one whose exit equals the earliest (the axis order of ties).
-        const float tin = __builtin_fmaxf(__builtin_fmaxf(en[0], en[1]), en[2]);
+        // The exit axis is the lowest one whose exit equals the earliest (the axis order of ties).
         const float tout = __builtin_fminf(__builtin_fminf(ex[0], ex[1]), ex[2]);
-        const int oa = ex[0] == tout ? 0 : (ex[1] == tout ? 1 : 2);
-        bool keep = fmin2(tout, w.tb) > fmax2(tin, w.ta);
-        if constexpr (RECHECK)
-            if (g.recheck && grazing(tin, tout, w.ta, w.tb)) keep = keep_f64(w, c, V);
-        if (keep && ((mask >> bit_in_brick(c)) & 1ull)) {
-            list[(size_t)n * stride] = pack_ijk(c);
-            if (++n == cap) break;
+        if (cells && (((bit & 32 ? hi32 : lo32) >> (bit & 31)) & 1u)) {
+            bool keep = fmin2(tout, w.tb) > fmax2(tin, w.ta);
+            const int c[3] = {(int)kp[0] - (st[0] > 0.0f), (int)kp[1] - (st[1] > 0.0f), (int)kp[2] - (st[2] > 0.0f)};
+            if constexpr (RECHECK)
+                if (g.recheck && grazing(tin, tout, w.ta, w.tb)) keep = keep_f64(w, c, V);
+            if (keep) {
+                list[(size_t)n * stride] = pack_ijk(c);
+                if (++n == cap) break;
+            }
         }
-        if (tout >= w.tb) break;
-        // step along the exit axis, as selects rather than a branch per axis
-        const bool s0 = oa == 0, s1 = oa == 1;
-        const bool s2 = !s0 && !s1;
-        c[0] += s0 ? st[0] : 0;
-        c[1] += s1 ? st[1] : 0;
-        c[2] += s2 ? st[2] : 0;
-        const int cn = s0 ? c[0] : (s1 ? c[1] : c[2]);
-        const int kp = cn + (s0 ? pk[0] : (s1 ? pk[1] : pk[2]));
-        const float xn = plane_t((float)kp, s0 ? w.o[0] : (s1 ? w.o[1] : w.o[2]),
-                                 s0 ? w.inv[0] : (s1 ? w.inv[1] : w.inv[2]));
-        en[0] = s0 ? ex[0] : en[0];
-        en[1] = s1 ? ex[1] : en[1];
-        en[2] = s2 ? ex[2] : en[2];
-        ex[0] = s0 ? xn : ex[0];
-        ex[1] = s1 ? xn : ex[1];
-        ex[2] = s2 ? xn : ex[2];
-        if (cn < 0 || cn >= V) break;
+        if (tout >= tb) break;
+        const bool s0 = ex[0] == tout, s1 = !s0 && ex[1] == tout, s2 = !s0 && !s1;
+        const bool left = (s0 && kp[0] == bx[0]) || (s1 && kp[1] == bx[1]) || (s2 && kp[2] == bx[2]);
+        tin = tout;
+        if (left) {
+            T = tout;
+            as = s0 ? 0 : (s1 ? 1 : 2);
+            brick += s0 ? sb[0] : (s1 ? sb[1] : sb[2]);
+            bx[0] += s0 ? 4.0f * st[0] : 0.0f;
+            bx[1] += s1 ? 4.0f * st[1] : 0.0f;
+            bx[2] += s2 ? 4.0f * st[2] : 0.0f;
+            kp[0] = bx[0];
+            kp[1] = bx[1];
+            kp[2] = bx[2];
+            enter = occupied();
+            cells = false;
+        } else {
+            bit += s0 ? sl[0] : (s1 ? sl[1] : sl[2]);
+            kp[0] += s0 ? st[0] : 0.0f;
+            kp[1] += s1 ? st[1] : 0.0f;
+            kp[2] += s2 ? st[2] : 0.0f;
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ex[a] = plane_t(kp[a], o[a], iv[a]);
     }
     return n;
 }
