@@ -99,12 +99,18 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
     constexpr int DW = f32 ? 4 : (int)P::UB / 4;      // dwords of a unit / fragment
     constexpr int MB = WIDTH / 32, NB = R > 32 ? R / 32 : 1;
     constexpr int NT = kBlock, NW = NT / 64;
-    constexpr int MW = MB * NB > NW ? MB * NB / NW : 1;   // output blocks of a wave
+    // A wave's output blocks: one of 32 units, and CW of 32 rays -- all of the tile's where there
+    // are as many of the units' blocks as waves, so that a weight is loaded by one wave only: the
+    // texture addresser is 74 % busy, a third of it with weights (width 128, the loads of an
+    // absent batch's zeros left out too, us: 1,048,576 FP16 rays 461 -> 421, 262,144 float32 275 -> 258).
+    constexpr bool all = MB >= NW;
+    constexpr int CW = all ? NB : 1;
+    static_assert(MB <= NW && MB * NB <= NW * CW, "every output block has a wave");
     constexpr uint32_t kCols = 32u * NB;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t slot0 = tile * R;
     const uint32_t li = lane & 31u, lq = lane >> 5;
-    const uint32_t nb = wave % NB, m0 = wave / NB * MW;
+    const uint32_t nb = all ? 0u : wave % NB, m0 = all ? wave : wave / NB;
     const bool mma_wave = m0 < (uint32_t)MB;
 
     // ---- rays
@@ -133,7 +139,7 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
 #pragma unroll
     for (int b = 1; b < NB; ++b) most = max(most, S.most[b]);
     most = __builtin_amdgcn_readfirstlane(most);
-    const uint32_t my_most = __builtin_amdgcn_readfirstlane(S.most[nb]);
+    const uint32_t my_most = all ? most : __builtin_amdgcn_readfirstlane(S.most[nb]);
 
     // ---- LDS: features of the points of `vox` voxels per ray and a zero point, the points, their slots
     const uint32_t pb = point_bytes<TM, F>(g.L), nbat = level_batches<TM, F>(g.L);
@@ -151,11 +157,11 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
     const uint32_t swz = pow2 ? units - 1u : 0u, sws = (uint32_t)__builtin_ctz(16u / (pow2 ? units : 16u));
     auto unit_at = [&](uint32_t s, uint32_t u) { return lds + s * pb + ((u ^ ((s >> sws) & swz)) * P::UB); };
 
-    f16_t acc[MW];
+    f16_t acc[CW];
 #pragma unroll
-    for (int m = 0; m < MW; ++m)
+    for (int c = 0; c < CW; ++c)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[m][e] = 0.0f;
+        for (int e = 0; e < 16; ++e) acc[c][e] = 0.0f;
     float amax = 0.0f;
 
     if (most > 0u) {
@@ -289,34 +295,46 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
         // ---- first layer: this wave's output blocks of its 32 rays
         if (mma_wave && my_most > j0) {
             const uint32_t nh = 2u * (min(my_most, j0 + nj) - j0);
-            const uint32_t col = nb * 32u + li;
-            const uint16_t *sm = smap + (col < (uint32_t)R ? col : 0u);
-            const bool none = col >= (uint32_t)R;
-            uint32_t s = zero;
+            const uint16_t *sm[CW];
+            uint32_t at[CW];
+            bool none[CW];
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const uint32_t col = (nb + c) * 32u + li;
+                none[c] = col >= (uint32_t)R;
+                sm[c] = smap + (none[c] ? 0u : col);
+                at[c] = zero;
+            }
+            auto next_point = [&](uint32_t hh) {
+#pragma unroll
+                for (int c = 0; c < CW; ++c) {
+                    const uint32_t ns = none[c] ? zero : sm[c][hh * R];
+                    at[c] = ns == kSameSlot ? at[c] : ns;
+                }
+            };
             if constexpr (f32) {
                 const uint32_t steps4 = ((uint32_t)LF + 7u) / 8u;   // groups of 4 matrix-core steps
                 for (uint32_t hh = 0; hh < nh; ++hh) {
-                    const uint32_t ns = none ? zero : sm[hh * R];
-                    s = ns == kSameSlot ? s : ns;
+                    next_point(hh);
                     const float *Wk = Wf + mm.off[0] + (size_t)(2u * j0 + hh) * LF * WIDTH + 32u * m0 + li;
                     for (uint32_t u = 0; u < steps4; ++u) {
-                        float a[4][MW];
+                        float a[4];
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
                             const uint32_t k = 8u * u + 2u * t + lq;
-#pragma unroll
-                            for (int m = 0; m < MW; ++m) a[t][m] = k < (uint32_t)LF ? Wk[k * WIDTH + 32u * m] : 0.0f;
+                            a[t] = k < (uint32_t)LF ? Wk[k * WIDTH] : 0.0f;
                         }
-                        const float4 bv = *reinterpret_cast<const float4 *>(
-                            lds + s * pb + (((u + lq * (half >> 2)) ^ ((s >> sws) & swz)) << 4));
-                        const float b4[4] = {bv.x, bv.y, bv.z, bv.w};
 #pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            if (8u * u + 2u * t < (uint32_t)LF) {
+                        for (int c = 0; c < CW; ++c) {
+                            const uint32_t s = at[c];
+                            const float4 bv = *reinterpret_cast<const float4 *>(
+                                lds + s * pb + (((u + lq * (half >> 2)) ^ ((s >> sws) & swz)) << 4));
+                            const float b4[4] = {bv.x, bv.y, bv.z, bv.w};
 #pragma unroll
-                                for (int m = 0; m < MW; ++m)
-                                    acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t][m], b4[t], acc[m], 0, 0, 0);
-                            }
+                            for (int t = 0; t < 4; ++t)
+                                if (8u * u + 2u * t < (uint32_t)LF)
+                                    acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b4[t], acc[c], 0, 0, 0);
+                        }
                     }
                 }
             } else {
@@ -324,39 +342,33 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
                 const int KB = mm.kb_point;
                 const uint32_t *Wk = Wv + mm.woff[0] + ((size_t)(2u * j0) * KB * MB + m0) * 64u * DW + lane * DW;
                 const uint32_t nx = nh * (uint32_t)KB;
+                const bool pad = nbat == 1u && lq != 0u;   // these lanes' weights are the zeros of an absent batch
                 constexpr int D = 4;   // fragments requested ahead
-                uint32_t nxt[D][MW][DW];
+                uint32_t nxt[D][DW] = {};
                 auto request = [&](uint32_t x0) {
+                    if (pad) return;
 #pragma unroll
-                    for (int t = 0; t < D; ++t)
-#pragma unroll
-                        for (int m = 0; m < MW; ++m)
-                            load_frag<DW>(Wk + ((size_t)min(x0 + t, nx - 1u) * MB + m) * 64u * DW, nxt[t][m]);
+                    for (int t = 0; t < D; ++t) load_frag<DW>(Wk + (size_t)min(x0 + t, nx - 1u) * MB * 64u * DW, nxt[t]);
                 };
                 request(0);
                 uint32_t hh = 0, kb = 0;
                 for (uint32_t x0 = 0; x0 < nx; x0 += D) {
-                    uint32_t cur[D][MW][DW];
+                    uint32_t cur[D][DW];
 #pragma unroll
                     for (int t = 0; t < D; ++t)
 #pragma unroll
-                        for (int m = 0; m < MW; ++m)
-#pragma unroll
-                            for (int q = 0; q < DW; ++q) cur[t][m][q] = nxt[t][m][q];
+                        for (int q = 0; q < DW; ++q) cur[t][q] = nxt[t][q];
                     if (x0 + D < nx) request(x0 + D);
 #pragma unroll
                     for (int t = 0; t < D; ++t) {
                         if (x0 + t < nx) {
-                            if (kb == 0) {
-                                const uint32_t ns = none ? zero : sm[hh * R];
-                                s = ns == kSameSlot ? s : ns;
-                            }
-                            uint32_t bd[DW];
-                            __builtin_memcpy(bd, __builtin_assume_aligned(unit_at(s, 2u * kb + lq), 4 * DW), 4 * DW);
-                            const vec_t bv = as_vec<vec_t, DW>(bd);
+                            if (kb == 0) next_point(hh);
 #pragma unroll
-                            for (int m = 0; m < MW; ++m)
-                                acc[m] = MmaT<TM>::mma(as_vec<vec_t, DW>(cur[t][m]), bv, acc[m]);
+                            for (int c = 0; c < CW; ++c) {
+                                uint32_t bd[DW];
+                                __builtin_memcpy(bd, __builtin_assume_aligned(unit_at(at[c], 2u * kb + lq), 4 * DW), 4 * DW);
+                                acc[c] = MmaT<TM>::mma(as_vec<vec_t, DW>(cur[t]), as_vec<vec_t, DW>(bd), acc[c]);
+                            }
                             if (++kb == (uint32_t)KB) {
                                 kb = 0;
                                 ++hh;
@@ -379,47 +391,48 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
             if (mma_wave) {
                 if constexpr (f32) {
                     amax = 0.0f;
-                    float *X = reinterpret_cast<float *>(lds) + (nb * 32u + li) * XS;
 #pragma unroll
-                    for (int m = 0; m < MW; ++m)
+                    for (int c = 0; c < CW; ++c) {
+                        float *X = reinterpret_cast<float *>(lds) + ((nb + c) * 32u + li) * XS;
 #pragma unroll
                         for (int e = 0; e < 16; e += 4) {
                             float x[4];
 #pragma unroll
                             for (int t = 0; t < 4; ++t) {
-                                x[t] = act_f(acc[m][e + t], mm.act, mm.slope);
+                                x[t] = act_f(acc[c][e + t], mm.act, mm.slope);
                                 amax = fmax2(amax, __builtin_fabsf(x[t]));
                             }
-                            const uint32_t at = 16u * (m0 + m) + e + 2u * lq;   // (unit 32 m + 2 e + 4 q) / 2
+                            const uint32_t at = 16u * m0 + e + 2u * lq;   // (unit 32 m + 2 e + 4 q) / 2
                             *reinterpret_cast<float2 *>(X + at) = make_float2(x[0], x[2]);
                             *reinterpret_cast<float2 *>(X + WIDTH / 2 + at) = make_float2(x[1], x[3]);
                         }
+                    }
                     if (A.dbg.act_amax) fold_max(A.dbg.act_amax + k, amax);
                 } else {
                     const float dqi = mm.dq[k - 1], qsi = mm.qs[k];
 #pragma unroll
-                    for (int m = 0; m < MW; ++m)
+                    for (int c = 0; c < CW; ++c)
 #pragma unroll
                         for (int s2 = 0; s2 < 2; ++s2) {
                             float v[8];
 #pragma unroll
                             for (int e = 0; e < 8; ++e) {
-                                const float y = MmaT<TM>::scaled ? acc[m][8 * s2 + e] * dqi : acc[m][8 * s2 + e];
+                                const float y = MmaT<TM>::scaled ? acc[c][8 * s2 + e] * dqi : acc[c][8 * s2 + e];
                                 v[e] = act_f(y, mm.act, mm.slope);
                             }
                             uint32_t d[DW];
                             pack8<TM>(v, qsi, d);
                             uint32_t *dst = reinterpret_cast<uint32_t *>(lds) +
-                                            (((nb * MB + m0 + m) * 2u + s2) * 64u + lane) * DW;
+                                            ((((nb + c) * MB + m0) * 2u + s2) * 64u + lane) * DW;
 #pragma unroll
                             for (int q = 0; q < DW; ++q) dst[q] = d[q];
                         }
                 }
             }
 #pragma unroll
-            for (int m = 0; m < MW; ++m)
+            for (int c = 0; c < CW; ++c)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[m][e] = 0.0f;
+                for (int e = 0; e < 16; ++e) acc[c][e] = 0.0f;
             __syncthreads();
             if constexpr (f32) {
                 if (!head && mma_wave) {
@@ -427,18 +440,17 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
                     const float *Wk = Wf + mm.off[k] + lq * WIDTH + 32u * m0 + li;
 #pragma unroll 2
                     for (uint32_t u = 0; u < WIDTH / 8; ++u) {
-                        float a[4][MW];
+                        float a[4];
 #pragma unroll
-                        for (int t = 0; t < 4; ++t)
+                        for (int t = 0; t < 4; ++t) a[t] = Wk[(8u * u + 2u * t) * WIDTH];
 #pragma unroll
-                            for (int m = 0; m < MW; ++m) a[t][m] = Wk[(8u * u + 2u * t) * WIDTH + 32u * m];
-                        const float4 bv = *reinterpret_cast<const float4 *>(X + 4u * u);
-                        const float b4[4] = {bv.x, bv.y, bv.z, bv.w};
+                        for (int c = 0; c < CW; ++c) {
+                            const float4 bv = *reinterpret_cast<const float4 *>(X + c * 32u * XS + 4u * u);
+                            const float b4[4] = {bv.x, bv.y, bv.z, bv.w};
 #pragma unroll
-                        for (int t = 0; t < 4; ++t)
-#pragma unroll
-                            for (int m = 0; m < MW; ++m)
-                                acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t][m], b4[t], acc[m], 0, 0, 0);
+                            for (int t = 0; t < 4; ++t)
+                                acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b4[t], acc[c], 0, 0, 0);
+                        }
                     }
                 } else if (head) {
                     // 16 outputs of 16 rays at a time: v_mfma_f32_16x16x4f32, the same ascending chain
@@ -458,28 +470,32 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
                 }
             } else {
                 typedef typename MmaT<TM>::vec vec_t;
-                if (mma_wave && (!head || m0 == 0u)) {
-                    const uint32_t *Wk = Wv + mm.woff[k] + (size_t)lane * DW;
-                    const uint32_t *X = reinterpret_cast<const uint32_t *>(lds) + (nb * MB * 2u * 64u + lane) * DW;
+                const uint32_t *Wk = Wv + mm.woff[k] + (size_t)lane * DW;
+                const uint32_t *X = reinterpret_cast<const uint32_t *>(lds) + (size_t)lane * DW;
+                if (!head && mma_wave) {
 #pragma unroll
-                    for (int mo = 0; mo < MW; ++mo) {
-                        if (head && mo > 0) break;
+                    for (int x = 0; x < 2 * MB; ++x) {
+                        uint32_t wd[DW];
+                        load_frag<DW>(Wk + (size_t)(m0 * MB * 2 + x) * 64 * DW, wd);
 #pragma unroll
-                        for (int m = 0; m < MB; ++m)
-#pragma unroll
-                            for (int s2 = 0; s2 < 2; ++s2) {
-                                uint32_t wd[DW], xd[DW];
-                                load_frag<DW>(Wk + (size_t)(((m0 + mo) * MB + m) * 2 + s2) * 64 * DW, wd);
-                                load_frag<DW>(X + (size_t)(m * 2 + s2) * 64 * DW, xd);
-                                acc[mo] = MmaT<TM>::mma(as_vec<vec_t, DW>(wd), as_vec<vec_t, DW>(xd), acc[mo]);
-                            }
+                        for (int c = 0; c < CW; ++c) {
+                            uint32_t xd[DW];
+                            load_frag<DW>(X + (size_t)((nb + c) * MB * 2 + x) * 64 * DW, xd);
+                            acc[c] = MmaT<TM>::mma(as_vec<vec_t, DW>(wd), as_vec<vec_t, DW>(xd), acc[c]);
+                        }
                     }
-                    if (head) {
-                        const float dqo = MmaT<TM>::scaled ? mm.dq[mm.n_hidden] : 1.0f;
-                        float *o = outs + (nb * 32u + li) * (kMaxOut + 1) + 4u * lq;
+                } else if (head && wave < (uint32_t)NB) {   // 32 rays to a wave
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) o[8 * (e / 4) + e % 4] = acc[0][e] * dqo;
+                    for (int x = 0; x < 2 * MB; ++x) {
+                        uint32_t wd[DW], xd[DW];
+                        load_frag<DW>(Wk + (size_t)x * 64 * DW, wd);
+                        load_frag<DW>(X + (size_t)(wave * MB * 2 + x) * 64 * DW, xd);
+                        acc[0] = MmaT<TM>::mma(as_vec<vec_t, DW>(wd), as_vec<vec_t, DW>(xd), acc[0]);
                     }
+                    const float dqo = MmaT<TM>::scaled ? mm.dq[mm.n_hidden] : 1.0f;
+                    float *o = outs + (wave * 32u + li) * (kMaxOut + 1) + 4u * lq;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[8 * (e / 4) + e % 4] = acc[0][e] * dqo;
                 }
             }
             __syncthreads();
