@@ -246,9 +246,9 @@ __device__ __forceinline__ float next_up(float x)
 // planes, then that axis's next one, a cell or a brick further), and the cell at which a brick
 // is entered is found only for bricks that hold voxels, without branches: the planes of each
 // axis that come before the entry are counted.  One lane per ray (us; finding the entry cell
-// of every brick with loops, then this): 1,048,576 rays at V = 32 237 and 157, 2,097,152 at
-// V = 128 447 and 233, 262,144 152 and 72, 1,000,003 diffuse ones 231 and 104.  Waiting until
-// 2, 4 or 16 lanes have a brick to enter: 241, 270 and 311 for 233.
+// of every brick with loops, then this): 1,048,576 rays at V = 32 237 and 150, 2,097,152 at
+// V = 128 447 and 226, 262,144 152 and 68, 1,000,003 diffuse ones 231 and 102.  Waiting until
+// 2, 4 or 16 lanes have a brick to enter: 241, 270 and 311 where this took 233.
 template <bool RECHECK>
 __device__ __forceinline__ int walk_voxels(const Geom &g, const VRay &w, const uint32_t *coarse,
                                            uint32_t *list, uint32_t stride, int cap)
@@ -324,9 +324,13 @@ __device__ __forceinline__ int walk_voxels(const Geom &g, const VRay &w, const u
             }
         }
         if (tout >= tb) break;
-        const bool s0 = ex[0] == tout, s1 = !s0 && ex[1] == tout, s2 = !s0 && !s1;
-        const bool left = (s0 && kp[0] == bx[0]) || (s1 && kp[1] == bx[1]) || (s2 && kp[2] == bx[2]);
+        const bool s0 = ex[0] == tout, s1 = !s0 & (ex[1] == tout), s2 = !s0 & !s1;
+        const bool left = (s0 & (kp[0] == bx[0])) | (s1 & (kp[1] == bx[1])) | (s2 & (kp[2] == bx[2]));
         tin = tout;
+        bit += s0 ? sl[0] : (s1 ? sl[1] : sl[2]);
+        kp[0] += s0 ? st[0] : 0.0f;
+        kp[1] += s1 ? st[1] : 0.0f;
+        kp[2] += s2 ? st[2] : 0.0f;
         if (left) {
             T = tout;
             as = s0 ? 0 : (s1 ? 1 : 2);
@@ -339,11 +343,6 @@ __device__ __forceinline__ int walk_voxels(const Geom &g, const VRay &w, const u
             kp[2] = bx[2];
             enter = occupied();
             cells = false;
-        } else {
-            bit += s0 ? sl[0] : (s1 ? sl[1] : sl[2]);
-            kp[0] += s0 ? st[0] : 0.0f;
-            kp[1] += s1 ? st[1] : 0.0f;
-            kp[2] += s2 ? st[2] : 0.0f;
         }
 #pragma unroll
         for (int a = 0; a < 3; ++a) ex[a] = plane_t(kp[a], o[a], iv[a]);
