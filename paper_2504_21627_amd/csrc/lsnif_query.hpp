@@ -314,16 +314,42 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
             };
             if constexpr (f32) {
                 const uint32_t steps4 = ((uint32_t)LF + 7u) / 8u;   // groups of 4 matrix-core steps
-                for (uint32_t hh = 0; hh < nh; ++hh) {
-                    next_point(hh);
-                    const float *Wk = Wf + mm.off[0] + (size_t)(2u * j0 + hh) * LF * WIDTH + 32u * m0 + li;
-                    for (uint32_t u = 0; u < steps4; ++u) {
-                        float a[4];
+                const uint32_t nx = nh * steps4;
+                const float *Wk = Wf + mm.off[0] + (size_t)(2u * j0) * LF * WIDTH + 32u * m0 + li;
+                // A small launch's few waves wait for every weight: two groups' are requested ahead
+                // (4,096 rays at 8 levels 33 -> 31 us with the registers below; no gain with more waves).
+                constexpr bool ahead = R == 16;
+                constexpr int D = ahead ? 2 : 1;
+                float nxt[D][4];
+                uint32_t ru = 0;
+                auto request = [&]() {   // the next D groups (one past the last is in the next layer's weights)
+#pragma unroll
+                    for (int g4 = 0; g4 < D; ++g4) {
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
-                            const uint32_t k = 8u * u + 2u * t + lq;
-                            a[t] = k < (uint32_t)LF ? Wk[k * WIDTH] : 0.0f;
+                            const uint32_t k = 8u * ru + 2u * t + lq;
+                            nxt[g4][t] = k < (uint32_t)LF ? Wk[k * WIDTH] : 0.0f;
                         }
+                        if (++ru == steps4) {
+                            ru = 0;
+                            Wk += LF * WIDTH;
+                        }
+                    }
+                };
+                if (ahead) request();
+                uint32_t hh = 0, u = 0;
+                for (uint32_t x0 = 0; x0 < nx; x0 += D) {
+                    if (!ahead) request();
+                    float a[D][4];
+#pragma unroll
+                    for (int g4 = 0; g4 < D; ++g4)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) a[g4][t] = nxt[g4][t];
+                    if (ahead && x0 + D < nx) request();
+#pragma unroll
+                    for (int g4 = 0; g4 < D; ++g4) {
+                        if (x0 + g4 >= nx) break;
+                        if (u == 0) next_point(hh);
 #pragma unroll
                         for (int c = 0; c < CW; ++c) {
                             const uint32_t s = at[c];
@@ -333,7 +359,11 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
 #pragma unroll
                             for (int t = 0; t < 4; ++t)
                                 if (8u * u + 2u * t < (uint32_t)LF)
-                                    acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b4[t], acc[c], 0, 0, 0);
+                                    acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g4][t], b4[t], acc[c], 0, 0, 0);
+                        }
+                        if (++u == steps4) {
+                            u = 0;
+                            ++hh;
                         }
                     }
                 }
@@ -518,8 +548,12 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
     decode_store<PAIRS>(A, mm, r, pair, w, count, o);
 }
 
+// Waves per SIMD that the registers leave room for.  float32 features of 2 need 145 registers;
+// held to 128 they spill, which costs large launches less than a fourth block gives
+// (524,288 rays 1,311 us for 1,362) and small ones 2 us.
+template <typename TF, int F, int R> constexpr int query_waves() { return sizeof(TF) == 4 && F == 2 && R == 16 ? 3 : 4; }
 template <typename TF, typename TM, int F, int WIDTH, bool PAIRS, int R>
-__global__ __launch_bounds__(kBlock, 4) void k_query(QueryArgs A, uint32_t lds_bytes)
+__global__ __launch_bounds__(kBlock, (query_waves<TF, F, R>())) void k_query(QueryArgs A, uint32_t lds_bytes)
 {
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];
     __shared__ QueryShared<R> S;
