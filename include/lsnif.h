@@ -572,8 +572,8 @@ lsnif_status lsnif_trainer_read(lsnif_trainer *tr, float *tables, float *const *
  * This call waits for those events and returns, summed over the steps since
  * the last read, the layer products' milliseconds (forward + backward) and the
  * scatter's, and the number of steps (any pointer may be NULL).  Objects whose
- * step after the voxel walk is one kernel (at most 48 32 x 32 blocks of weight
- * gradients) report that kernel and the partial sums as the products, the scatter
+ * step after the voxel walk is one kernel (at most 36 32 x 32 blocks of weight
+ * gradients; with more than 128 inputs, batches of 4,096 rays and more) report that kernel and the partial sums as the products, the scatter
  * in it, as 0. */
 lsnif_status lsnif_train_profile_read(lsnif_trainer *tr, double *products_ms, double *scatter_ms,
                                       uint32_t *steps);

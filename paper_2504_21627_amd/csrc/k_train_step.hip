@@ -108,7 +108,7 @@ __device__ __forceinline__ f16_t product(const float *w, uint32_t ld, const floa
 }
 
 template <int F, int WIDTH, int MAXB>
-__global__ __launch_bounds__(kBlock, MAXB <= 9 ? 2 : 1) void k_train_fused(TrainStepArgs A, uint32_t SX)
+__global__ __launch_bounds__(kBlock, 2) void k_train_fused(TrainStepArgs A, uint32_t SX)
 {
     constexpr uint32_t R = kStepRows, MB = WIDTH / 32, SA = WIDTH + 4;
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -385,8 +385,7 @@ static hipError_t step_go(const TrainStepArgs &A, uint32_t in0, hipStream_t s)
     const uint32_t nb = A.first[A.n_hidden + 1], lds = (uint32_t)step_lds_bytes(in0, A.n_hidden, WIDTH), SX = x_stride(in0);
     const dim3 grid(step_blocks(A.L.n));
     if (nb <= 4u * 5u) hipLaunchKernelGGL((k_train_fused<F, WIDTH, 5>), grid, dim3(kBlock), lds, s, A, SX);
-    else if (nb <= 4u * 9u) hipLaunchKernelGGL((k_train_fused<F, WIDTH, 9>), grid, dim3(kBlock), lds, s, A, SX);
-    else hipLaunchKernelGGL((k_train_fused<F, WIDTH, 12>), grid, dim3(kBlock), lds, s, A, SX);
+    else hipLaunchKernelGGL((k_train_fused<F, WIDTH, 9>), grid, dim3(kBlock), lds, s, A, SX);
     return hipGetLastError();
 }
 

@@ -87,9 +87,9 @@ template <int R> __device__ __forceinline__ uint32_t block_subtile(uint32_t tile
 // product and sum is what a ray alone would get, in the same order, whatever its tile.
 // Points are taken `vox` voxels of every ray at a time, as many as the LDS holds.
 // Measured (ms, a ray per lane before / now): 2,097,152 rays FP16 1.90 / 1.71, 1,000,003 FP8
-// 0.99 / 0.70, 39,999 0.204 / 0.115, 256 0.046 / 0.020; float32 MLPs, then on the vector ALU
-// with weights from scalar loads: 524,288 rays of width 64 2.40 / 1.24, 262,144 of width 128
-// 2.09 / 0.34.
+// 0.99 / 0.66, 39,999 0.204 / 0.115, 256 0.046 / 0.018; float32 MLPs, then on the vector ALU
+// with weights from scalar loads: 524,288 rays of width 64 2.40 / 1.16, 262,144 of width 128
+// 2.09 / 0.25.
 template <typename TF, typename TM, int F, int WIDTH, bool PAIRS, int R>
 __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, const Mlp &mm, const TF *__restrict__ tab,
                                           QueryShared<R> &S, char *lds, uint32_t lds_bytes, uint32_t tile)

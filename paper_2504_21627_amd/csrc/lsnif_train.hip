@@ -99,15 +99,20 @@ uint32_t grad_blocks(const Object &ob, int k)
     return (k ? mb : (in0 + 31u) / 32u) * (k == ob.mlp.n_hidden ? 1u : mb);
 }
 
-// Whether one kernel holds a step of the object: its weight gradients in 12 accumulator blocks
-// per wave, its activations in LDS.
-bool fused(const Object &ob)
+// Whether one kernel takes a step of n rays: the weight gradients fit 9 accumulator blocks per
+// wave beside two blocks to a CU, the activations the LDS; and, as a tile's encoding and
+// scatter are serial work in proportion to the inputs, batches of an object with many are
+// large (us, separate launches and this: 288 inputs, 2,000 rays 303 and 344, 4,096 373 and 344,
+// 65,536 2,250 and 1,410; 108 inputs, 32 rays 169 and 153).  12 blocks per wave (576 inputs, one
+// block to a CU): 2,000 rays 784 and 1,095, 16,384 1,100 and 1,165, 131,072 3,806 and 3,270.
+bool fused(const Object &ob, uint32_t n)
 {
     uint32_t blocks = 0;
     for (int k = 0; k <= ob.mlp.n_hidden; ++k) blocks += grad_blocks(ob, k);
     const uint32_t in0 = (uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F);
-    return blocks <= 48u && 4u * (uint32_t)ob.geom.H <= (uint32_t)(ob.mlp.n_hidden * (ob.width + 4)) &&
-           step_lds_bytes(in0, (uint32_t)ob.mlp.n_hidden, (uint32_t)ob.width) <= (150u << 10);
+    return blocks <= 36u && (in0 <= 128u || n >= 4096u) &&
+           4u * (uint32_t)ob.geom.H <= (uint32_t)(ob.mlp.n_hidden * (ob.width + 4)) &&
+           step_lds_bytes(in0, (uint32_t)ob.mlp.n_hidden, (uint32_t)ob.width) <= (78u << 10);
 }
 
 // Floats of the transposed weights: layer 0's rows padded to 32 j.
@@ -134,7 +139,7 @@ uint32_t wgrad_chunk(uint32_t M, uint32_t N, uint32_t n)
 // scratch of their two-pass sum.
 size_t part_floats(const Object &ob, uint32_t n)
 {
-    if (fused(ob)) return ((size_t)step_blocks(n) + kSumGroups) * weight_floats(ob) + trans_floats(ob);
+    if (fused(ob, n)) return ((size_t)step_blocks(n) + kSumGroups) * weight_floats(ob) + trans_floats(ob);
     const uint32_t in0 = (uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F), Wd = (uint32_t)ob.width;
     size_t best = 0;
     for (int k = 0; k <= ob.mlp.n_hidden; ++k) {
@@ -148,8 +153,8 @@ size_t part_floats(const Object &ob, uint32_t n)
 size_t step_ws_bytes(const Object &ob, uint32_t n)
 {
     const size_t in = (size_t)ob.geom.H * ob.geom.L * ob.geom.F, od = (size_t)ob.mlp.out_dim;
-    const size_t acts = fused(ob) ? 0 : al256((size_t)n * in * 4) + (size_t)ob.mlp.n_hidden * al256((size_t)n * ob.width * 4);
-    const size_t outs = fused(ob) ? al256((order_ws_words(n) + 1) * 4) : 2 * al256((size_t)n * od * 4);
+    const size_t acts = fused(ob, n) ? 0 : al256((size_t)n * in * 4) + (size_t)ob.mlp.n_hidden * al256((size_t)n * ob.width * 4);
+    const size_t outs = fused(ob, n) ? al256((order_ws_words(n) + 1) * 4) : 2 * al256((size_t)n * od * 4);
     return al256((size_t)n * (ob.geom.H / 2) * 4) + al256(n) + acts + outs +
            al256(part_floats(ob, n) * 4) + al256(((size_t)n + kStepRows - 1) / kStepRows * 4);
 }
@@ -163,7 +168,7 @@ StepWs carve(const Object &ob, uint32_t n, void *ws)
     w += al256((size_t)n * (ob.geom.H / 2) * 4);
     S.nvox = reinterpret_cast<uint8_t *>(w);
     w += al256(n);
-    if (fused(ob)) {
+    if (fused(ob, n)) {
         S.sort = reinterpret_cast<uint32_t *>(w);
         w += al256((order_ws_words(n) + 1) * 4);
     } else {
@@ -202,7 +207,7 @@ lsnif_status grads(lsnif_trainer *tr, const Object &ob, const lsnif_ray *d_rays,
     float *tab = static_cast<float *>(ob.d_tab);
     float *W = static_cast<float *>(const_cast<void *>(ob.d_w));
     float *gtab = tr->grad, *gW = tr->grad + tr->copies * tr->n_tab;
-    const bool one = fused(ob);
+    const bool one = fused(ob, n);
     uint32_t *n_live = one ? S.sort + order_ws_words(n) : nullptr;
     HIP_TRY(launch_train_fill(gtab, tr->copies * tr->n_tab, gW, tr->n_w, n_live, s));
     // voxel lists: the query path's walk, rays in their given order

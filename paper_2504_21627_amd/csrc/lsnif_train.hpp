@@ -127,7 +127,7 @@ struct TrainStepArgs {
     uint32_t n_w;
     float *loss_part;         // one float per block of the launch
 };
-// Rows a block takes at once; blocks of a launch over n rays; its dynamic LDS for an object (0:
+// Rows a block takes at once; blocks of a launch over n rays (two to a CU); its dynamic LDS for an object (0:
 // the object does not fit the kernel) with in0 inputs, nh hidden layers of `width`.
 constexpr uint32_t kStepRows = 32;
 inline uint32_t step_blocks(uint32_t n) { return (n + kStepRows - 1) / kStepRows < 512u ? (n + kStepRows - 1) / kStepRows : 512u; }

@@ -1,5 +1,5 @@
-"""The training step's kernel at the edges of its tiles (32 rays), of its register blocks (20, 36
-and 48 32 x 32 blocks of weight gradient, one more: the separate products) and of its ray order
+"""The training step's kernel at the edges of its tiles (32 rays), of its register blocks (20
+and 36 32 x 32 blocks of weight gradient, more: the separate products) and of its ray order
 (2^18 rays), against the training oracle.
 
 An entry's error is held against the layer's (or the tables') largest entry, 1e-5 of it, the
@@ -22,8 +22,8 @@ SHAPES = {   # L, F, H, hidden layers, width, R, activation
     "one hidden layer": (2, 3, 16, 1, 64, [20, 48], RELU),
     "36 blocks": (2, 3, 18, 2, 128, [64, 100], LEAKY_RELU),
     "odd inputs": (3, 2, 14, 2, 128, [8, 32, 77], RELU),
-    "44 blocks": (1, 3, 14, 3, 128, [96], LEAKY_RELU),
-    "one block too many": (2, 3, 18, 3, 128, [64, 128], LEAKY_RELU),
+    "more blocks": (1, 3, 14, 3, 128, [96], LEAKY_RELU),
+    "many more blocks": (2, 3, 18, 3, 128, [64, 128], LEAKY_RELU),
 }
 
 
@@ -55,9 +55,11 @@ def test_step_at_tile_edges(L, mesh, name):   # noqa: F811
             check_norm(gW[k], ref["gW"][k], ref["gW_abs"][k], f"layer {k}, {n} rays")
 
 
-def test_step_of_more_rays_than_two_launches_order(L, mesh):   # noqa: F811
-    """A batch given many times over has its own mean loss and gradients."""
-    obj = W.configs.paper_object(seed=11)
+@pytest.mark.parametrize("which", ["paper", "c1"])
+def test_step_of_more_rays_than_two_launches_order(L, mesh, which):   # noqa: F811
+    """A batch given many times over has its own mean loss and gradients (c1: 288 inputs, which
+    only large batches bring to the one kernel)."""
+    obj = W.configs.paper_object(seed=11) if which == "paper" else W.configs.c1_object(seed=2)
     rays, tg = WT.batch(mesh, obj, 2000, seed=33)
     rays, tg = subset(rays, tg, margin_keep(obj, rays, tg))
     ref = OT.train_grads(obj, rays, tg, bounds=True)
@@ -67,6 +69,7 @@ def test_step_of_more_rays_than_two_launches_order(L, mesh):   # noqa: F811
     assert len(r) > 1 << 18
     loss, gtab, gW, _, _, _ = gpu_grads(L, obj, r, t)
     assert abs(loss - ref["loss"]) <= 1e-5 * ref["loss"], (loss, ref["loss"])
-    check_grad(gtab, ref["gtab"], ref["gtab_abs"], "tables")
+    check = check_grad if which == "paper" else check_norm
+    check(gtab, ref["gtab"], ref["gtab_abs"], "tables")
     for k in range(len(gW)):
-        check_grad(gW[k], ref["gW"][k], ref["gW_abs"][k], f"layer {k}")
+        check(gW[k], ref["gW"][k], ref["gW_abs"][k], f"layer {k}")
