@@ -65,32 +65,36 @@ __global__ __launch_bounds__(kBlock) void k_walk_wide(QueryArgs A)
     }
 }
 
-// By the launch's slots n.  64 lanes per ray and a plane per lane up to 8,192 slots (4,096 rays:
+// By the launch's slots n and its largest grid V.  64 lanes per ray and a plane per lane up to 8,192 slots (4,096 rays:
 // 16 us at V = 32, 19 at 128; 8 lanes and bricks: 24 and 42; 16,000 rays at V = 128: 48 and
-// 40), 8 lanes and a brick boundary per lane up to 57,344, one lane beyond: its chain (40 us at
+// 40), then a brick boundary per lane: 16 lanes up to 32,768 where V is 128 or more (16,000 rays at
+// V = 128 40 and, 16 lanes, 32, at V = 32 24 and 29; 40,000 at 128 42 and 47; 16,000 pairs at V up
+// to 256 58 and 40), 8 up to 57,344, one lane beyond: its chain (40 us at
 // V = 32, 66 at 128, 105 at 256) takes as long for few rays as for a chip full (us, 8 lanes and
 // one: V = 32, 40,000 slots 36 and 38, 80,000 59 and 41; V = 128, 64,000 62 and 66, 128,000 93 and
 // 68; pairs at V up to 256, 24,000 78 and 103, 154,000 170 and 112).
 template <bool PAIRS, bool RECHECK>
-static void go(const QueryArgs &A, uint32_t grid, hipStream_t s)
+static void go(const QueryArgs &A, uint32_t max_V, uint32_t grid, hipStream_t s)
 {
     const uint32_t n = grid * kBlock;
     if (n <= 8192u)
         hipLaunchKernelGGL((k_walk_wide<PAIRS, RECHECK, 64, true>), dim3(grid * 64u), dim3(kBlock), 0, s, A);
+    else if (n <= 32768u && max_V >= 128u)
+        hipLaunchKernelGGL((k_walk_wide<PAIRS, RECHECK, 16, false>), dim3(grid * 16u), dim3(kBlock), 0, s, A);
     else if (n <= 57344u)
         hipLaunchKernelGGL((k_walk_wide<PAIRS, RECHECK, 8, false>), dim3(grid * 8u), dim3(kBlock), 0, s, A);
     else
         hipLaunchKernelGGL((k_walk<PAIRS, RECHECK>), dim3(grid), dim3(kBlock), 0, s, A);
 }
 
-hipError_t launch_walk(const QueryArgs &A, bool pairs, bool recheck, uint32_t grid, hipStream_t s)
+hipError_t launch_walk(const QueryArgs &A, bool pairs, bool recheck, uint32_t max_V, uint32_t grid, hipStream_t s)
 {
     if (pairs) {
-        if (recheck) go<true, true>(A, grid, s);
-        else go<true, false>(A, grid, s);
+        if (recheck) go<true, true>(A, max_V, grid, s);
+        else go<true, false>(A, max_V, grid, s);
     } else {
-        if (recheck) go<false, true>(A, grid, s);
-        else go<false, false>(A, grid, s);
+        if (recheck) go<false, true>(A, max_V, grid, s);
+        else go<false, false>(A, max_V, grid, s);
     }
     return hipGetLastError();
 }

@@ -656,13 +656,13 @@ size_t pairs_ws_bytes(uint32_t n_rays, uint32_t n_pairs, uint32_t n_objs, uint32
 // kernel (gather bound).  `ev_mid`, when timing, is recorded once the query
 // kernel may start.
 template <typename Query>
-static lsnif_status walk_then_query(lsnif_ctx *ctx, QueryArgs A, bool pairs, bool recheck,
+static lsnif_status walk_then_query(lsnif_ctx *ctx, QueryArgs A, bool pairs, bool recheck, uint32_t max_V,
                                     uint32_t ntiles, uint32_t chunks, hipStream_t s, hipEvent_t ev_mid, Query &&query)
 {
     const uint32_t k = std::max(1u, std::min(chunks, ntiles / kMinChunkTiles));
     if (k == 1) {
         A.tile0 = 0;
-        HIP_TRY(launch_walk(A, pairs, recheck, ntiles, s));
+        HIP_TRY(launch_walk(A, pairs, recheck, max_V, ntiles, s));
         if (ev_mid) HIP_TRY(hipEventRecord(ev_mid, s));
         HIP_TRY(query(A, ntiles));
         return LSNIF_OK;
@@ -683,7 +683,7 @@ static lsnif_status walk_then_query(lsnif_ctx *ctx, QueryArgs A, bool pairs, boo
     HIP_TRY(hipStreamWaitEvent(ctx->side, ev[0], 0));
     for (uint32_t i = 0; i < k; ++i) {
         A.tile0 = first(i);
-        HIP_TRY(launch_walk(A, pairs, recheck, first(i + 1) - first(i), ctx->side));
+        HIP_TRY(launch_walk(A, pairs, recheck, max_V, first(i + 1) - first(i), ctx->side));
         HIP_TRY(hipEventRecord(ev[i + 1], ctx->side));
     }
     for (uint32_t i = 0; i < k; ++i) {
@@ -752,7 +752,7 @@ lsnif_status enqueue_query(lsnif_ctx *ctx, const Object &ob, const lsnif_ray *d_
         return launch_query_fp8(a, ob.feat_dtype, ob.F, L, false, g, s);
     };
     const uint32_t k = dbg ? 1u : (chunks > 0 ? (uint32_t)chunks : ob.walk_chunks);
-    lsnif_status st = walk_then_query(ctx, A, false, ob.geom.recheck != 0, grid, k, s, ev[2], query);
+    lsnif_status st = walk_then_query(ctx, A, false, ob.geom.recheck != 0, (uint32_t)ob.geom.V, grid, k, s, ev[2], query);
     if (st) return st;
     if (ev[3]) {
         HIP_TRY(hipEventRecord(ev[3], s));
@@ -804,6 +804,7 @@ lsnif_status pairs_setup(lsnif_ctx *ctx, PairsSetup &ps)
                                          "(feature type, MLP type, F, width)");
         ps.maxH = std::max(ps.maxH, kv.second.geom.H);
         ps.max_L = std::max(ps.max_L, kv.second.geom.L);
+        ps.max_V = std::max(ps.max_V, (uint32_t)kv.second.geom.V);
         ps.recheck = ps.recheck || kv.second.geom.recheck;
         ps.walk_chunks = std::max(ps.walk_chunks, kv.second.walk_chunks);
         ps.pair_bits = std::max(ps.pair_bits, kv.second.geom.pair_bits);
@@ -893,7 +894,7 @@ lsnif_status enqueue_pairs(lsnif_ctx *ctx, const PairsSetup &ps, const lsnif_ray
         A.nvox = nvox;
         A.lists = lists;
         const uint32_t k = chunks > 0 ? (uint32_t)chunks : ps.walk_chunks;
-        lsnif_status st = walk_then_query(ctx, A, true, ps.recheck, n_tiles, k, s, ev[2],
+        lsnif_status st = walk_then_query(ctx, A, true, ps.recheck, ps.max_V, n_tiles, k, s, ev[2],
                                           [&](const QueryArgs &a, uint32_t g) -> hipError_t {
             const int L = ps.max_L;
             if (first.mlp_dtype == LSNIF_FP32) return launch_query_f32(a, first.feat_dtype, first.F, L, true, g, s);

@@ -135,6 +135,7 @@ struct PairsSetup {
     const Object *first = nullptr;
     int maxH = 2;
     int max_L = 1;          // most levels of the objects
+    uint32_t max_V = 1;     // largest voxel grid of the objects
     bool recheck = false;   // some object re-decides grazing voxels in float64
     uint32_t walk_chunks = 1;   // largest walk_chunks of the objects
     uint32_t pair_bits = 1;     // finest pair grouping of the objects

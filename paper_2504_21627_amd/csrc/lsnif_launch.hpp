@@ -41,8 +41,9 @@ hipError_t launch_query_f16(const QueryArgs &A, int feat_dtype, int F, int max_L
 hipError_t launch_query_bf16(const QueryArgs &A, int feat_dtype, int F, int max_L, bool pairs, uint32_t grid, hipStream_t s);
 hipError_t launch_query_fp8(const QueryArgs &A, int feat_dtype, int F, int max_L, bool pairs, uint32_t grid, hipStream_t s);
 // Voxel walk of every slot into A.lists / A.nvox, before the query kernel of the same `grid`;
-// `recheck` when some object of the launch re-decides grazing voxels in float64.
-hipError_t launch_walk(const QueryArgs &A, bool pairs, bool recheck, uint32_t grid, hipStream_t s);
+// `recheck` when some object of the launch re-decides grazing voxels in float64; max_V: the
+// largest grid of its objects.
+hipError_t launch_walk(const QueryArgs &A, bool pairs, bool recheck, uint32_t max_V, uint32_t grid, hipStream_t s);
 hipError_t launch_debug(const DebugArgs &D, hipStream_t s);
 // Gather ceiling: the query's gathers alone, each ray's feature sum into sums[r].
 hipError_t launch_gather_only(const QueryArgs &A, int feat_dtype, int F, float *sums, uint32_t grid, hipStream_t s);

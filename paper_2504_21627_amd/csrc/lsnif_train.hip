@@ -217,7 +217,7 @@ lsnif_status grads(lsnif_trainer *tr, const Object &ob, const lsnif_ray *d_rays,
     A.n = n;
     A.lists = S.lists;
     A.nvox = S.nvox;
-    HIP_TRY(launch_walk(A, false, ob.geom.recheck != 0, (n + kBlock - 1) / kBlock, s));
+    HIP_TRY(launch_walk(A, false, ob.geom.recheck != 0, (uint32_t)ob.geom.V, (n + kBlock - 1) / kBlock, s));
     TrainEncArgs E{};
     E.g = ob.geom;
     E.rays = A.rays;

@@ -49,7 +49,7 @@ def test_lists_equal_the_serial_walk(V, density, recheck):
         # one lane per ray: past the last switch
         serial = encodings(ctx, oid, obj, np.resize(base, (57344 + 257, 8)))
         assert np.array_equal(serial["count"][:len(base)], oracle.query(obj, base, debug=True)["count"])
-        for n in (1, 63, len(base), 8192, 8193, 57344):
+        for n in (1, 63, len(base), 8192, 8193, 32769, 57344):
             got = encodings(ctx, oid, obj, np.resize(base, (n, 8)))
             for k, v in got.items():
                 assert v.tobytes() == serial[k][:n].tobytes(), (n, k)
