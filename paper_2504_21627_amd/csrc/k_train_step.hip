@@ -51,12 +51,51 @@ __global__ __launch_bounds__(kBlock) void k_train_transpose(TrainStepArgs A, uin
     if (c < ld) A.WT[A.offT[k] + i] = u < in ? A.W[A.off[k] + u * ld + c] : 0.0f;
 }
 
-constexpr uint32_t kZ = 20;   // floats of a row of outputs or their gradients (16 used)
-static uint32_t x_stride(uint32_t in0) { return (in0 + 31u) / 32u * 32u + 4u; }
-
-size_t step_lds_bytes(uint32_t in0, uint32_t nh, uint32_t width)
+// 32 x 32 products of a row-major weight matrix (lane's column at w, rows ld apart, lane half
+// q starting at row q) and 32 rows in LDS (lane's row at `in`): acc += w[k] in[k] over its `rows`
+// rows, ascending.  a: the first 8 weights, loaded before the barrier ahead of the product; the
+// next 8 travel while 8 are multiplied.  TAIL: `rows` need not be a multiple of 16; the last
+// ones are multiplied with weights of 0 after them (step_weight_row).
+__device__ __forceinline__ void first_weights(const float *w, uint32_t ld, float a[8])
 {
-    return 4u * (size_t)(kStepRows * (x_stride(in0) + nh * (width + 4u) + 2u * kZ) + 32u);
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j) a[j] = w[2u * j * ld];
+}
+
+__device__ __forceinline__ void multiply8(f16_t &acc, const float a[8], const float *in, uint32_t q)
+{
+#pragma unroll
+    for (uint32_t j = 0; j < 8; j += 2) {
+        const float4 b = *reinterpret_cast<const float4 *>(in + 2u * j);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], q ? b.y : b.x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j + 1], q ? b.w : b.z, acc, 0, 0, 0);
+    }
+}
+
+template <bool TAIL>
+__device__ __forceinline__ f16_t product(const float *w, uint32_t ld, const float *in, uint32_t rows, uint32_t q, float a[8])
+{
+    const uint32_t K = TAIL ? rows / 16u * 16u : rows;
+    f16_t acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+    for (uint32_t c = 0; c < K; c += 16u) {
+        float next[8];
+        first_weights(w + (size_t)(c + 16u < K ? c + 16u : 0u) * ld, ld, next);
+        multiply8(acc, a, in + c, q);
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j) a[j] = next[j];
+    }
+    if (TAIL && K < rows) {
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j) {
+            const uint32_t row = K + 2u * j + q;
+            const float x = w[(int)(step_weight_row(row, rows) - q) * (int)ld];
+            a[j] = row < rows ? x : 0.0f;
+        }
+        multiply8(acc, a, in + K, q);
+    }
+    return acc;
 }
 
 // One block takes tiles of 32 rows (rays), dealt in turn from the longest lists to the shortest.
@@ -66,8 +105,8 @@ size_t step_lds_bytes(uint32_t in0, uint32_t nh, uint32_t width)
 // head's forward one 16x16x4), the forward ones in ascending K, so the outputs are what
 // layer-by-layer products give, bit for bit.  Of the encoding only the points of the tile's
 // longest list are formed, multiplied and given gradients, and rays that list nothing are not
-// in the order.  (A weight that is not finite therefore spoils the rays that use it, not
-// every gradient at once.)
+// in the order.  (A first-layer weight that is not finite therefore spoils the tiles that reach its
+// point, not every gradient at once.)
 //
 // Separate launches moved every activation and gradient through HBM and multiplied the zeros:
 // at 262,144 rays of the paper's default object (173,070 list voxels) 916 us of products, 57 of
@@ -77,36 +116,6 @@ size_t step_lds_bytes(uint32_t in0, uint32_t nh, uint32_t width)
 // the rest is the waves' serial phases (rays, encoding, head, losses: 32 k of 110 k cycles a
 // tile) at the two waves per SIMD that the accumulators leave room for.  Tiles in coherence order
 // instead: 589 for 505, the blocks' padding and ends being less even.
-// 32 x 32 products of a row-major weight matrix (lane's column at w, rows ld apart, lane half
-// q starting at row q) and 32 rows in LDS (lane's row at `in`): acc += w[k] in[k], K
-// (a multiple of 16) ascending.  a: the first 8 weights, loaded before the barrier
-// ahead of the product; the next 8 travel while 8 are multiplied.
-__device__ __forceinline__ void first_weights(const float *w, uint32_t ld, float a[8])
-{
-#pragma unroll
-    for (uint32_t j = 0; j < 8; ++j) a[j] = w[2u * j * ld];
-}
-
-__device__ __forceinline__ f16_t product(const float *w, uint32_t ld, const float *in, uint32_t K, uint32_t q, float a[8])
-{
-    f16_t acc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-    for (uint32_t c = 0; c < K; c += 16u) {
-        float next[8];
-        first_weights(w + (size_t)(c + 16u < K ? c + 16u : 0u) * ld, ld, next);
-#pragma unroll
-        for (uint32_t j = 0; j < 8; j += 2) {
-            const float4 b = *reinterpret_cast<const float4 *>(in + c + 2u * j);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], q ? b.y : b.x, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j + 1], q ? b.w : b.z, acc, 0, 0, 0);
-        }
-#pragma unroll
-        for (uint32_t j = 0; j < 8; ++j) a[j] = next[j];
-    }
-    return acc;
-}
-
 template <int F, int WIDTH, int MAXB>
 __global__ __launch_bounds__(kBlock, 2) void k_train_fused(TrainStepArgs A, uint32_t SX)
 {
@@ -116,7 +125,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_train_fused(TrainStepArgs A, uint
     __shared__ uint32_t s_mov[R], s_nv[R], s_row[R], s_most;
     const Geom &g = A.L.g;
     const uint32_t nh = A.n_hidden, LF = (uint32_t)g.L * F, in0 = (uint32_t)g.H * LF;
-    float *X = lds, *Act = X + R * SX, *Z = Act + nh * R * SA, *Gz = Z + R * kZ;
+    float *X = lds, *Act = X + R * SX, *Z = Act + nh * R * SA, *Gz = Z + R * kStepZ;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t li = lane & 31u, lq = lane >> 5;
     const uint32_t rows = *A.n_live, tiles = (rows + R - 1u) / R;
@@ -219,7 +228,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_train_fused(TrainStepArgs A, uint
             first_weights(Wk, WIDTH, wa);
             __syncthreads();
             if (wave < MB) {
-                const f16_t acc = product(Wk, WIDTH, k ? act_of(k) + li * SA : X + li * SX, k ? (uint32_t)WIDTH : K1r, lq, wa);
+                const f16_t acc = product<true>(Wk, WIDTH, k ? act_of(k) + li * SA : X + li * SX, k ? (uint32_t)WIDTH : K1, lq, wa);
                 float *O = act_of(k + 1u) + li * SA + 32u * wave + 4u * lq;
 #pragma unroll
                 for (int e = 0; e < 16; e += 4) {
@@ -240,19 +249,19 @@ __global__ __launch_bounds__(kBlock, 2) void k_train_fused(TrainStepArgs A, uint
 #pragma unroll 8
             for (uint32_t c = 0; c < WIDTH; c += 4u)
                 o4 = __builtin_amdgcn_mfma_f32_16x16x4f32(Wk[c * kMaxOut], I[c], o4, 0, 0, 0);
-            *reinterpret_cast<float4 *>(Z + (16u * wave + i16) * kZ + 4u * q4) = make_float4(o4[0], o4[1], o4[2], o4[3]);
+            *reinterpret_cast<float4 *>(Z + (16u * wave + i16) * kStepZ + 4u * q4) = make_float4(o4[0], o4[1], o4[2], o4[3]);
         }
         __syncthreads();
 
         // ---- losses and their gradients
         if (tid < R) {
-            float *d = Gz + tid * kZ;
+            float *d = Gz + tid * kStepZ;
 #pragma unroll
             for (uint32_t k = 0; k < kMaxOut; ++k) d[k] = 0.0f;
             float l = 0.0f;
             if (live) {
                 const lsnif_train_target y = A.L.gt[ray];
-                l = ray_loss(A.L, y, ta, tb, Z + tid * kZ, d);
+                l = ray_loss(A.L, y, ta, tb, Z + tid * kStepZ, d);
 #pragma unroll
                 for (uint32_t k = 0; k < kMaxOut; ++k) d[k] *= inv_n;
             }
@@ -267,7 +276,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_train_fused(TrainStepArgs A, uint
             float *I = k ? act_of(ku) : X;
             const uint32_t SI = k ? SA : SX;
             const float *G = ku == nh ? Gz : act_of(ku + 1u);
-            const uint32_t SG = ku == nh ? kZ : SA, nN = ku == nh ? 1u : MB;
+            const uint32_t SG = ku == nh ? kStepZ : SA, nN = ku == nh ? 1u : MB;
             // weight gradient: input^T x G over the rows
 #pragma unroll
             for (int i = 0; i < MAXB; ++i) {
@@ -296,7 +305,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_train_fused(TrainStepArgs A, uint
                     const float *Wt = A.WT + A.offT[k] + lq * ldT + 32u * m + li;
                     float wa[8];
                     first_weights(Wt, ldT, wa);
-                    acc = product(Wt, ldT, G + li * SG, ld, lq, wa);
+                    acc = product<false>(Wt, ldT, G + li * SG, ld, lq, wa);
                 }
                 __syncthreads();   // the weight gradients have read the layer's input
                 if (!mine) continue;
@@ -382,7 +391,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_train_fused(TrainStepArgs A, uint
 template <int F, int WIDTH>
 static hipError_t step_go(const TrainStepArgs &A, uint32_t in0, hipStream_t s)
 {
-    const uint32_t nb = A.first[A.n_hidden + 1], lds = (uint32_t)step_lds_bytes(in0, A.n_hidden, WIDTH), SX = x_stride(in0);
+    const uint32_t nb = A.first[A.n_hidden + 1], lds = (uint32_t)step_lds_bytes(in0, A.n_hidden, WIDTH), SX = step_x_stride(in0);
     const dim3 grid(step_blocks(A.L.n));
     if (nb <= 4u * 5u) hipLaunchKernelGGL((k_train_fused<F, WIDTH, 5>), grid, dim3(kBlock), lds, s, A, SX);
     else hipLaunchKernelGGL((k_train_fused<F, WIDTH, 9>), grid, dim3(kBlock), lds, s, A, SX);

@@ -92,27 +92,16 @@ struct StepWs {
     uint32_t *sort;   // the fused step's ray order (order_ws_words(n) words), then the number of its rows
 };
 
-// Blocks of 32 x 32 of layer k's weight gradient.
 uint32_t grad_blocks(const Object &ob, int k)
 {
-    const uint32_t mb = (uint32_t)ob.width / 32u, in0 = (uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F);
-    return (k ? mb : (in0 + 31u) / 32u) * (k == ob.mlp.n_hidden ? 1u : mb);
+    const uint32_t in0 = (uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F);
+    return step_grad_blocks(in0, (uint32_t)ob.mlp.n_hidden, (uint32_t)ob.width, (uint32_t)k);
 }
 
-// Whether one kernel takes a step of n rays: the weight gradients fit 9 accumulator blocks per
-// wave beside two blocks to a CU, the activations the LDS; and, as a tile's encoding and
-// scatter are serial work in proportion to the inputs, batches of an object with many are
-// large (us, separate launches and this: 288 inputs, 2,000 rays 303 and 344, 4,096 373 and 344,
-// 65,536 2,250 and 1,410; 108 inputs, 32 rays 169 and 153).  12 blocks per wave (576 inputs, one
-// block to a CU): 2,000 rays 784 and 1,095, 16,384 1,100 and 1,165, 131,072 3,806 and 3,270.
 bool fused(const Object &ob, uint32_t n)
 {
-    uint32_t blocks = 0;
-    for (int k = 0; k <= ob.mlp.n_hidden; ++k) blocks += grad_blocks(ob, k);
     const uint32_t in0 = (uint32_t)(ob.geom.H * ob.geom.L * ob.geom.F);
-    return blocks <= 36u && (in0 <= 128u || n >= 4096u) &&
-           4u * (uint32_t)ob.geom.H <= (uint32_t)(ob.mlp.n_hidden * (ob.width + 4)) &&
-           step_lds_bytes(in0, (uint32_t)ob.mlp.n_hidden, (uint32_t)ob.width) <= (78u << 10);
+    return step_takes(in0, (uint32_t)ob.geom.H, (uint32_t)ob.mlp.n_hidden, (uint32_t)ob.width, n);
 }
 
 // Floats of the transposed weights: layer 0's rows padded to 32 j.

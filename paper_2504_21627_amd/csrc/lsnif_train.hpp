@@ -127,11 +127,40 @@ struct TrainStepArgs {
     uint32_t n_w;
     float *loss_part;         // one float per block of the launch
 };
-// Rows a block takes at once; blocks of a launch over n rays (two to a CU); its dynamic LDS for an object (0:
-// the object does not fit the kernel) with in0 inputs, nh hidden layers of `width`.
+// Rows a block takes at once; blocks of a launch over n rays (two to a CU).
 constexpr uint32_t kStepRows = 32;
 inline uint32_t step_blocks(uint32_t n) { return (n + kStepRows - 1) / kStepRows < 512u ? (n + kStepRows - 1) / kStepRows : 512u; }
-size_t step_lds_bytes(uint32_t in0, uint32_t nh, uint32_t width);
+// Floats of a tile's row of inputs, and of outputs or their gradients (16 used); the kernel's dynamic
+// LDS for an object with in0 inputs, nh hidden layers of `width`.
+constexpr uint32_t kStepZ = 20;
+inline uint32_t step_x_stride(uint32_t in0) { return (in0 + 31u) / 32u * 32u + 4u; }
+inline size_t step_lds_bytes(uint32_t in0, uint32_t nh, uint32_t width)
+{
+    return 4u * (size_t)(kStepRows * (step_x_stride(in0) + nh * (width + 4u) + 2u * kStepZ) + 32u);
+}
+// Blocks of 32 x 32 of layer k's weight gradient.
+inline uint32_t step_grad_blocks(uint32_t in0, uint32_t nh, uint32_t width, uint32_t k)
+{
+    const uint32_t mb = width / 32u;
+    return (k ? mb : (in0 + 31u) / 32u) * (k == nh ? 1u : mb);
+}
+// Whether one kernel takes a step of n rays: the weight gradients fit 9 accumulator blocks per
+// wave beside two blocks to a CU, the activations the LDS; and, as a tile's encoding and
+// scatter are serial work in proportion to the inputs, batches of an object with many are
+// large (us, separate launches and this: 288 inputs, 2,000 rays 303 and 344, 4,096 373 and 344,
+// 65,536 2,250 and 1,410; 108 inputs, 32 rays 169 and 153).  12 blocks per wave (576 inputs, one
+// block to a CU): 2,000 rays 784 and 1,095, 16,384 1,100 and 1,165, 131,072 3,806 and 3,270.
+inline bool step_takes(uint32_t in0, uint32_t H, uint32_t nh, uint32_t width, uint32_t n)
+{
+    uint32_t blocks = 0;
+    for (uint32_t k = 0; k <= nh; ++k) blocks += step_grad_blocks(in0, nh, width, k);
+    return blocks <= 36u && (in0 <= 128u || n >= 4096u) && 4u * H <= nh * (width + 4u) &&
+           step_lds_bytes(in0, nh, width) <= (78u << 10);
+}
+// The row that a lane reads for row `row` of a matrix of `rows` rows.  The first layer's product runs
+// over the inputs in use, padded to 32, and the packed weights end with the head's 16 rows: with one
+// hidden layer the rows past the inputs would lie past the allocation.
+__host__ __device__ inline uint32_t step_weight_row(uint32_t row, uint32_t rows) { return row < rows ? row : rows - 1u; }
 hipError_t launch_train_step(const TrainStepArgs &A, uint32_t F, uint32_t width, hipStream_t s);
 // Order of the rays that list voxels (at most `most`), longest lists first, in ws
 // (order_ws_words(n) words, 16-byte aligned); *n_live (0 before) receives their number.
