@@ -336,7 +336,8 @@ lsnif_status lsnif_bounce(lsnif_ctx *ctx, const lsnif_ray *d_rays, const lsnif_h
  *                 then share 256-ray tiles (the work decomposition of Sec. 4:
  *                 dispatch sorted rays rather than scattered ones).  Until it
  *                 is set, found by lsnif_autotune or read from the cache, an
- *                 object whose tables take at most 4 MiB is not sorted.
+ *                 object whose tables take at most 4 MiB is not sorted
+ *                 and reports 0 (larger ones 5).
  *  pair_bits      the same grouping, 2^pair_bits cells per axis (1..5), or at 6
  *                 by the cell alone (64 cells per axis, no octant), for the
  *                 object's pairs in pair queries, within the object's tiles.

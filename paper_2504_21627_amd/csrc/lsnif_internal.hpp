@@ -48,7 +48,7 @@ struct Object {
     uint32_t hot_budget = 0;      // the tuning's hot_lds_bytes and persistent: kept and reported, nothing reads them
     uint32_t walk_chunks = kWalkChunks;    // tile ranges of a query whose walk runs ahead
     uint32_t persistent = 0;
-    bool tuned = false;           // sort_bits was set, found or cached for the object
+    bool tuned = false;           // sort_bits was set, found or cached for the object (else its default, see query_sort_bits)
     uint64_t bytes = 0;
     // bits of the coherence sort that a query of the object runs (0: none)
     uint32_t query_sort_bits() const

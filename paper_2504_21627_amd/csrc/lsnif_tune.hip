@@ -40,9 +40,11 @@ void apply_tuning(lsnif_ctx *ctx, Object &ob, const lsnif_tuning &t)
     ++ctx->generation;
 }
 
+// sort_bits as the object's queries run: 0 where it was not chosen and its default is left out, so
+// that what is reported or cached can be set again and changes nothing.
 lsnif_tuning object_tuning(const Object &ob)
 {
-    return lsnif_tuning{(int32_t)ob.geom.sort_bits, (int32_t)ob.geom.pair_bits, (int32_t)ob.hot_budget,
+    return lsnif_tuning{(int32_t)ob.query_sort_bits(), (int32_t)ob.geom.pair_bits, (int32_t)ob.hot_budget,
                         (int32_t)ob.walk_chunks, (int32_t)ob.persistent};
 }
 
@@ -139,6 +141,7 @@ lsnif_status lsnif_autotune(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray 
     HIP_TRY(hipDeviceSynchronize());
     const lsnif_tuning start = current(ob);
     const bool was_tuned = ob.tuned;
+    const uint32_t was_bits = ob.geom.sort_bits;
     lsnif_tuning win = start;
     float win_ms = -1.0f;
     ob.tuned = true;   // the candidates' sort_bits hold
@@ -171,6 +174,7 @@ lsnif_status lsnif_autotune(lsnif_ctx *ctx, uint32_t object_id, const lsnif_ray 
     apply(ctx, ob, st ? start : win);
     if (st) {
         ob.tuned = was_tuned;
+        ob.geom.sort_bits = was_bits;
         return st;
     }
     *best = win;
@@ -192,7 +196,10 @@ lsnif_status lsnif_autotune_pairs(lsnif_ctx *ctx, const lsnif_ray *d_rays, uint3
     DeviceGuard guard(ctx->device);
     HIP_TRY(hipDeviceSynchronize());
     std::vector<std::pair<uint32_t, lsnif_tuning>> start;
-    for (auto &kv : ctx->objects) start.push_back({kv.first, current(kv.second)});
+    for (auto &kv : ctx->objects) {
+        start.push_back({kv.first, current(kv.second)});
+        start.back().second.sort_bits = (int32_t)kv.second.geom.sort_bits;   // as kept, chosen or not
+    }
     auto apply_all = [&](const lsnif_tuning &t) {
         for (auto &kv : ctx->objects)
             apply(ctx, kv.second,
