@@ -330,7 +330,9 @@ __global__ __launch_bounds__(kBlock) void k_adam(AdamArgs A)
         const float v = A.b2 * A.v[i] + (1.0f - A.b2) * (g * g);
         A.m[i] = m;
         A.v[i] = v;
-        A.p[i] = A.p[i] - A.lr * (m * A.c1) / (sqrtf(v * A.c2) + A.eps);
+        const float p = A.p[i] - A.lr * (m * A.c1) / (sqrtf(v * A.c2) + A.eps);
+        A.p[i] = p;
+        if (i < A.n_odd && inf_or_nan(p)) *A.odd = 1u;
     }
 }
 

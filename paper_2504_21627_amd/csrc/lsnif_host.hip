@@ -85,6 +85,15 @@ void store_elem(void *dst, size_t i, float v, int dtype)
     else static_cast<uint8_t *>(dst)[i] = f32_to_e4m3(v);
 }
 
+// Whether element i of dtype is an infinity or not a number.
+bool odd_elem(const void *src, size_t i, int dtype)
+{
+    if (dtype == LSNIF_FP32) return !std::isfinite(static_cast<const float *>(src)[i]);
+    if (dtype == LSNIF_FP16) return (static_cast<const uint16_t *>(src)[i] & 0x7c00u) == 0x7c00u;
+    if (dtype == LSNIF_BF16) return (static_cast<const uint16_t *>(src)[i] & 0x7f80u) == 0x7f80u;
+    return (static_cast<const uint8_t *>(src)[i] & 0x7fu) == 0x7fu;
+}
+
 int out_dim_of(const lsnif_object_desc *d) { return 5 + 3 * (d->has_albedo ? 1 : 0) + d->n_mat; }
 
 lsnif_status validate(const lsnif_object_desc *d)
@@ -405,6 +414,12 @@ lsnif_status lsnif_build(lsnif_ctx *ctx, const lsnif_object_desc *d, uint32_t *o
     }
     std::vector<uint8_t> wbytes(wf.size() * dtype_size(wdt));
     for (size_t i = 0; i < wf.size(); ++i) store_elem(wbytes.data(), i, wf[i], wdt);
+    bool odd = false;
+    for (size_t i = 0; i < (size_t)ob.mlp.off[1]; ++i) {
+        if (!odd_elem(wbytes.data(), i, wdt)) continue;
+        odd = true;
+        if (wdt != LSNIF_FP32) store_elem(wbytes.data(), i, 0.0f, wdt);
+    }
     if (wdt != LSNIF_FP32)
         for (int k = 0; k <= d->n_hidden; ++k) ob.mlp.woff[k] = (int32_t)((size_t)ob.mlp.off[k] * dtype_size(wdt) / 4);
     ob.bytes = occ_bytes + tab.size() + wbytes.size();
@@ -416,7 +431,21 @@ lsnif_status lsnif_build(lsnif_ctx *ctx, const lsnif_object_desc *d, uint32_t *o
         (void)hipFree(ob.d_tab);
         (void)hipFree(ob.d_w);
     };
-    tab.resize(tab.size() + kTablePad, 0);   // not counted in the footprint
+    // not counted in the footprint: spare bytes after the tables; after the weights the word that says
+    // that some of the first layer are not finite and, where those are not in the weights
+    // themselves (FP32, which training may move there), the layer with them alone
+    const size_t odd_at = (wbytes.size() + 15) / 16 * 16;
+    const size_t in0 = (size_t)d->H * d->L * d->F, odd_n = odd && wdt != LSNIF_FP32 ? in0 * d->width : 0;
+    tab.resize(tab.size() + kTablePad, 0);
+    wbytes.resize(odd_at + 16 + odd_n * 4, 0);
+    wbytes[odd_at] = odd ? 1 : 0;
+    for (size_t k = 0; k < odd_n; ++k) {
+        const float w = d->W[0][(k % d->width) * in0 + k / d->width];
+        uint8_t q[4];
+        store_elem(q, 0, w, wdt);
+        const float x = odd_elem(q, 0, wdt) ? (std::isnan(w) ? w : std::copysign(INFINITY, w)) : 0.0f;
+        memcpy(wbytes.data() + odd_at + 16 + 4 * k, &x, 4);
+    }
     if (hipMalloc(&ob.d_occ, occ_bytes) != hipSuccess || hipMalloc(&ob.d_tab, tab.size()) != hipSuccess ||
         hipMalloc(&ob.d_w, wbytes.size()) != hipSuccess) {
         cleanup();
@@ -432,6 +461,10 @@ lsnif_status lsnif_build(lsnif_ctx *ctx, const lsnif_object_desc *d, uint32_t *o
     g.coarse = reinterpret_cast<const uint32_t *>(g.fine + nbricks);
     Mlp &m = ob.mlp;
     m.W = ob.d_w;
+    m.odd = odd ? 1u : 0u;
+    m.odd_at = reinterpret_cast<uint32_t *>(static_cast<char *>(ob.d_w) + odd_at);
+    m.odd_w = reinterpret_cast<const float *>(wdt == LSNIF_FP32 ? static_cast<char *>(ob.d_w)
+                                                               : static_cast<char *>(ob.d_w) + odd_at + 16);
     m.n_hidden = d->n_hidden;
     m.out_dim = out_dim_of(d);
     m.act = d->act;

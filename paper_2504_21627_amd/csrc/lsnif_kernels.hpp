@@ -29,6 +29,9 @@ struct Mlp {
     int32_t n_mat, has_albedo;
     int32_t kb_point;         // matrix-core path: K blocks (16 wide) per boundary point
     int32_t fp;               // matrix-core path: features per level after padding
+    uint32_t odd;             // matrix-core path: not 0 if some first-layer weight is not finite
+    uint32_t *odd_at;         // float32 path: the same, kept after the weights, which training moves
+    const float *odd_w;       // then: the first layer as [inputs][width], read for those weights
     int32_t woff[8];          // matrix-core path: dword offset of each layer's fragments
     float qs[8];              // FP8: 1 / activation scale of each layer's input (1 otherwise)
     float dq[8];              // FP8: weight scale x activation scale of each layer (1 otherwise)

@@ -95,6 +95,7 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
                                           QueryShared<R> &S, char *lds, uint32_t lds_bytes, uint32_t tile)
 {
     typedef PointT<TM, F> P;
+    typedef const __attribute__((address_space(4))) uint32_t cword;
     constexpr bool f32 = P::f32;
     constexpr int DW = f32 ? 4 : (int)P::UB / 4;      // dwords of a unit / fragment
     constexpr int MB = WIDTH / 32, NB = R > 32 ? R / 32 : 1;
@@ -156,6 +157,21 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
     const bool pow2 = (units & (units - 1u)) == 0u && units <= 16u && P::UB == 16u;
     const uint32_t swz = pow2 ? units - 1u : 0u, sws = (uint32_t)__builtin_ctz(16u / (pow2 ? units : 16u));
     auto unit_at = [&](uint32_t s, uint32_t u) { return lds + s * pb + ((u ^ ((s >> sws) & swz)) * P::UB); };
+    auto feature_at = [&](uint32_t s, uint32_t k) -> float {   // feature k of point s, as stored
+        if constexpr (f32) {
+            const uint32_t x = k / 2u + (k & 1u) * half;
+            return reinterpret_cast<const float *>(lds + s * pb)[(((x >> 2) ^ ((s >> sws) & swz)) << 2) | (x & 3u)];
+        } else {
+            const uint32_t ks = k / F * P::FP + k % F;
+            const uint32_t *d = reinterpret_cast<const uint32_t *>(unit_at(s, ks >> 3));
+            if constexpr (DW == 4) {
+                const uint32_t x = d[(ks & 7u) >> 1];
+                return (ks & 1u) ? hi16<TM>(x) : lo16<TM>(x);
+            } else {
+                return __builtin_amdgcn_cvt_f32_fp8((int)(d[(ks & 7u) >> 2] >> (8u * (ks & 3u))), 0);
+            }
+        }
+    };
 
     f16_t acc[CW];
 #pragma unroll
@@ -224,6 +240,9 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
             if (has) pts[s1] = make_float4(p1[0], p1[1], p1[2], __int_as_float(f1));
         }
         __syncthreads();
+        // whether some first-layer weight is not finite; training moves those of FP32 on the device
+        uint32_t odd = mm.odd;
+        if constexpr (f32) odd = *(cword *)mm.odd_at;   // through the scalar path, needed after the features
         // ---- features: a wave takes 64 points and one batch of levels at a time
         const uint32_t npts = __builtin_amdgcn_readfirstlane(S.npts);
         const uint32_t tasks = (npts + 63u) / 64u * nbat;
@@ -274,20 +293,8 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
                 if (s == kSameSlot) s = smap[i - R];
                 const uint32_t dst = A.order ? A.order[rr] : rr;
                 for (int k = 0; k < LF; ++k) {
-                    float v;
-                    if constexpr (f32) {
-                        const uint32_t x = (uint32_t)k / 2u + ((uint32_t)k & 1u) * half;
-                        v = reinterpret_cast<const float *>(lds + s * pb)[(((x >> 2) ^ ((s >> sws) & swz)) << 2) | (x & 3u)];
-                    } else {
-                        const uint32_t ks = (uint32_t)(k / F * P::FP + k % F);
-                        const uint32_t *d = reinterpret_cast<const uint32_t *>(unit_at(s, ks >> 3));
-                        if constexpr (DW == 4) {
-                            const uint32_t x = d[(ks & 7u) >> 1];
-                            v = (ks & 1u) ? hi16<TM>(x) : lo16<TM>(x);
-                        } else {
-                            v = __builtin_amdgcn_cvt_f32_fp8((int)(d[(ks & 7u) >> 2] >> (8u * (ks & 3u))), 0) / mm.qs[0];
-                        }
-                    }
+                    float v = feature_at(s, (uint32_t)k);
+                    if constexpr (!f32 && DW == 2) v /= mm.qs[0];
                     A.dbg.enc[((size_t)dst * g.H + h) * LF + k] = v;
                 }
             }
@@ -345,6 +352,13 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
                     for (int g4 = 0; g4 < D; ++g4)
 #pragma unroll
                         for (int t = 0; t < 4; ++t) a[g4][t] = nxt[g4][t];
+                    if (__builtin_expect(odd != 0u, 0)) {   // made finite, see below
+#pragma unroll
+                        for (int g4 = 0; g4 < D; ++g4)
+#pragma unroll
+                            for (int t = 0; t < 4; ++t)
+                                a[g4][t] = __builtin_amdgcn_fmed3f(a[g4][t], -3.402823466e38f, 3.402823466e38f);
+                    }
                     if (ahead && x0 + D < nx) request();
 #pragma unroll
                     for (int g4 = 0; g4 < D; ++g4) {
@@ -403,6 +417,33 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
                                 kb = 0;
                                 ++hh;
                             }
+                        }
+                    }
+                }
+            }
+            // Rays whose points have run out took the zero point, and 0 times a weight that is not finite
+            // is not 0: the weights above are finite, and where the object has others (rarely),
+            // the rays' own points meet those here.
+            if (__builtin_expect(odd != 0u, 0)) {
+                uint32_t q4 = 4u * lq;
+                asm volatile("" : "+v"(q4));   // nothing of this is kept in registers for the common way
+#pragma unroll
+                for (int c = 0; c < CW; ++c) {
+                    const float *Wo = mm.odd_w + (size_t)(2u * j0) * LF * WIDTH + 32u * m0 + q4;
+                    const uint32_t col = (nb + c) * 32u + li;
+                    uint32_t s = zero;
+#pragma unroll 1
+                    for (uint32_t i = 0; i < nh * (uint32_t)LF; ++i, Wo += WIDTH) {
+                        const uint32_t hh = i / (uint32_t)LF, k = i - hh * (uint32_t)LF;
+                        const uint32_t ns = col < (uint32_t)R ? smap[hh * R + col] : zero;
+                        s = ns == kSameSlot ? s : ns;
+                        const float x = feature_at(s, k);
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            if (__builtin_amdgcn_ballot_w64(inf_or_nan(Wo[8 * (e / 4) + e % 4])) == 0ull) continue;
+                            const float w = Wo[8 * (e / 4) + e % 4];
+                            acc[c][e] = inf_or_nan(w) && s != zero ? __builtin_fmaf(x, w, acc[c][e]) : acc[c][e];
+                            asm volatile("" ::: "memory");
                         }
                     }
                 }

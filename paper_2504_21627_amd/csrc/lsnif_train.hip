@@ -372,6 +372,8 @@ lsnif_status apply(lsnif_trainer *tr, const Object &ob, hipStream_t s)
     A.m = tr->m + tr->n_tab;
     A.v = tr->v + tr->n_tab;
     A.count = tr->n_w;
+    A.odd = ob.mlp.odd_at;
+    A.n_odd = (uint64_t)ob.mlp.off[1];
     HIP_TRY(launch_adam(A, s));
     tr->steps = t;
     return LSNIF_OK;

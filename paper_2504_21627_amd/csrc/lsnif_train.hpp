@@ -105,6 +105,8 @@ struct AdamArgs {
     const float *g;
     uint64_t count;
     float lr, b1, b2, eps, c1, c2;   // c1 = 1 / (1 - b1^t), c2 = 1 / (1 - b2^t)
+    uint32_t *odd;                   // set if one of the first n_odd parameters leaves the finite numbers (for good)
+    uint64_t n_odd;
 };
 
 // One training step's forward and backward passes after the walk, in one kernel.
