@@ -368,14 +368,15 @@ __device__ __forceinline__ void encode_aligned(const Geom &g, const TF *__restri
 #pragma unroll
     for (int lv = 0; lv < NL; ++lv) {
         const float u0 = 1.0f - wu[lv], u1 = wu[lv], v0 = 1.0f - wv[lv], v1 = wv[lv];
-        const float w3 = u1 * v1, wl = up[lv] ? w3 : 0.0f;
+        const float w3 = u1 * v1;
 #pragma unroll
         for (int f = 0; f < F; ++f) {
             float s = __builtin_fmaf(u0 * v0, e[lv][0].get(f), 0.0f);
             s = __builtin_fmaf(u1 * v0, e[lv][1].get(f), s);
             s = __builtin_fmaf(u0 * v1, e[lv][2].get(f), s);
-            const float a = up[lv] ? s : __builtin_fmaf(w3, e[lv][3].get(f), s);
-            out[lv][f] = H16 ? fma_f16(wl, e[lv][3].get(f), a) : __builtin_fmaf(wl, e[lv][3].get(f), a);
+            const float x3 = e[lv][3].get(f), a = up[lv] ? s : __builtin_fmaf(w3, x3, s);
+            const float xl = up[lv] ? x3 : 0.0f;   // not a weight of 0: x3 may be infinite
+            out[lv][f] = H16 ? fma_f16(w3, xl, a) : __builtin_fmaf(w3, xl, a);
         }
         if (l0 + lv >= g.L) {
 #pragma unroll

@@ -1,5 +1,5 @@
-"""Weights that are not finite, on inputs of the later boundary points: a ray that lists few voxels
-does not use them, and its answer does not depend on the rays beside it."""
+"""Weights and table entries that are not finite.  Weights on inputs of the later boundary points: a ray
+that lists few voxels does not use them, and its answer does not depend on the rays beside it."""
 import copy
 
 import numpy as np
@@ -44,3 +44,42 @@ def test_short_rays_do_not_meet_the_weights_of_later_points(feat, mlp, F, levels
                 assert np.array_equal(a, b), (k, n)
     finally:
         L.lsnif_destroy(ctx)
+
+
+@pytest.mark.parametrize("feat,mlp", [("fp32", "fp32"), ("fp16", "fp16"), ("bf16", "fp32")])
+def test_infinite_entries_on_aligned_levels(feat, mlp):
+    """Three features per level: a level aligned with the voxel faces gives the features that it gives
+    beside one that is not aligned, infinities included (the sums over a face's 4 corners and
+    over all 8, of which 4 weigh nothing)."""
+    import torch
+    from tests.test_oracle_pins import tiny_object, adversarial_rays
+    torch.cuda.init()
+    rng = np.random.default_rng(11)
+    V = 16
+    occ = rng.uniform(size=V ** 3) < 0.4
+    rays = adversarial_rays(rng, V, n_random=600).astype(np.float32)
+    enc = []
+    ctx = L.lsnif_create(0)
+    try:
+        for last in (2 * V, 2 * V + 1):
+            obj = tiny_object(V, occ, H=18, L=2, F=3, R=[V, last], log2_T=13, width=64, n_hidden=2, seed=4)
+            at = np.random.default_rng(5).integers(1, 1 << 13, 600)
+            obj.tables[0, at, at % 3] = np.where(at & 4, np.inf, -np.inf)
+            oid = L.lsnif_build(ctx, L.ObjectDesc(obj, feat, mlp))
+            enc.append(run_enc(ctx, oid, obj, rays)[:, :, 0, :])
+    finally:
+        L.lsnif_destroy(ctx)
+    print(feat, mlp, "infinite features", int(np.isinf(enc[1]).sum()), "not a number", int(np.isnan(enc[1]).sum()), flush=True)
+    assert np.isinf(enc[1]).sum() > 500
+    assert np.array_equal(enc[0], enc[1], equal_nan=True)
+
+
+def run_enc(ctx, oid, obj, rays):
+    import torch
+    n = len(rays)
+    r = torch.from_numpy(rays).cuda()
+    out = torch.empty((n, 6), dtype=torch.float32, device="cuda")
+    enc = torch.zeros((n, obj.H * obj.L * obj.F), dtype=torch.float32, device="cuda")
+    L.lsnif_query_debug(ctx, oid, r, out, {"enc": enc})
+    torch.cuda.synchronize()
+    return enc.cpu().numpy().reshape(n, obj.H, obj.L, obj.F)
