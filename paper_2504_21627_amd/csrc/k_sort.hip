@@ -286,12 +286,13 @@ hipError_t launch_coherence_sort(const Geom &g, const float4 *rays, uint32_t n, 
     if (passes > kRadixMaxPasses) return hipErrorInvalidValue;
     uint32_t *k0 = ws, *v0 = k0 + n, *k1 = v0 + n, *v1 = k1 + n, *hist = v1 + n;
     // Two passes of 10-bit digits: 4 launches where three passes of 8 bits take 12 (40,000 rays
-    // 62 -> 36 us, 262,144 69 -> 49).  The first pass's counters lie in v0 and the second's in k0, both
-    // free then (at most n / 2 + 1,024 words each).
+    // 62 -> 36 us, 262,144 69 -> 49).  The first pass's counters lie in v0 (group_counts_at) and the
+    // second's in k0, both free then (at most n / 2 + 1,024 words each).
     const uint32_t top = sort_bins(g.sort_bits) - 1u;
-    if (n >= kRadixTile && n <= kGroupMax && top < kGroupDigits * kGroupDigits) {
-        hipLaunchKernelGGL(k_group_keys, dim3(nblk), dim3(kGroupDigits), 0, s, g, rays, n, k0, v0);
-        hipLaunchKernelGGL(k_group_scatter, dim3(nblk), dim3(kBlock), 0, s, k0, nullptr, k1, v1, n, v0, kGroupDigits, 0u);
+    if (n >= 2u * kRadixTile && n <= kGroupMax && top < kGroupDigits * kGroupDigits) {
+        uint32_t *c0 = ws + group_counts_at(n);
+        hipLaunchKernelGGL(k_group_keys, dim3(nblk), dim3(kGroupDigits), 0, s, g, rays, n, k0, c0);
+        hipLaunchKernelGGL(k_group_scatter, dim3(nblk), dim3(kBlock), 0, s, k0, nullptr, k1, v1, n, c0, kGroupDigits, 0u);
         const uint32_t digits = (top >> kGroupBits) + 1u;
         const hipError_t e = launch_digit_count(k1, n, k0, kGroupBits, digits, s);
         if (e != hipSuccess) return e;

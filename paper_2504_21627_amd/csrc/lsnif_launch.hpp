@@ -32,6 +32,10 @@ __host__ __device__ inline size_t radix_ws_words(uint32_t n) { return 4u * (size
 // digits whose blocks read the counters of all blocks (block-major, `digits` per block)
 // and sum them themselves: no launches for the scans.
 constexpr uint32_t kGroupMax = 1u << 18, kGroupDigits = 1024, kGroupBits = 10;
+// Where the coherence sort of n rays (n >= 2 kRadixTile) keeps its first pass's counters: words from the
+// start of its workspace, after the keys, in the second of its four arrays of n words, which the
+// pass does not use.  The counters are read 16 bytes at a time, so they start at such a boundary.
+__host__ __device__ inline size_t group_counts_at(uint32_t n) { return ((size_t)n + 3u) / 4u * 4u; }
 struct Geom;
 struct QueryArgs;
 struct DebugArgs;
@@ -77,7 +81,7 @@ hipError_t launch_radix_pass(const uint32_t *sk, const uint32_t *sv, uint32_t *d
 // The counts of the digit (key >> shift, below `digits`) of each block's items, block-major.
 hipError_t launch_digit_count(const uint32_t *sk, uint32_t n, uint32_t *hist, uint32_t shift, uint32_t digits,
                               hipStream_t s);
-// One grouping pass of at most kGroupMax items by such a digit, with those counts.
+// One grouping pass of at most kGroupMax items by such a digit, with those counts (16-byte aligned).
 hipError_t launch_group_scatter(const uint32_t *sk, const uint32_t *sv, uint32_t *dk, uint32_t *dv, uint32_t n,
                                 const uint32_t *hist, uint32_t digits, uint32_t shift, hipStream_t s);
 // Sorts rays 0..n-1 by coherence key in `ws` (radix_ws_words(n) words);
