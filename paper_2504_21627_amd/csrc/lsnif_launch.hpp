@@ -36,6 +36,9 @@ constexpr uint32_t kGroupMax = 1u << 18, kGroupDigits = 1024, kGroupBits = 10;
 // start of its workspace, after the keys, in the second of its four arrays of n words, which the
 // pass does not use.  The counters are read 16 bytes at a time, so they start at such a boundary.
 __host__ __device__ inline size_t group_counts_at(uint32_t n) { return ((size_t)n + 3u) / 4u * 4u; }
+// Tiles that one launch takes at most, at `threads` work-items a tile: HIP counts a launch's work-items
+// in 32 bits.
+inline uint32_t tiles_per_launch(uint32_t threads) { return 0xffffffffu / threads; }
 struct Geom;
 struct QueryArgs;
 struct DebugArgs;

@@ -616,14 +616,20 @@ __global__ __launch_bounds__(kBlock, (query_waves<TF, F, R>())) void k_query(Que
 constexpr uint32_t kQueryLds = 37u << 10;
 
 template <typename TF, typename TM, int F, int WIDTH, int R>
-inline void query_go(const QueryArgs &A, int max_L, bool pairs, uint32_t grid, hipStream_t s)
+inline void query_go(QueryArgs A, int max_L, bool pairs, uint32_t grid, hipStream_t s)
 {
     uint32_t vox = (uint32_t)A.g.H / 2u;
     while (vox > 1u && query_lds_bytes<TM, F, WIDTH, R>(max_L, vox) > kQueryLds) --vox;
     const uint32_t lds = query_lds_bytes<TM, F, WIDTH, R>(max_L, vox);
-    const dim3 blocks(grid * (kBlock / R));
-    if (pairs) hipLaunchKernelGGL((k_query<TF, TM, F, WIDTH, true, R>), blocks, dim3(kBlock), lds, s, A, lds);
-    else hipLaunchKernelGGL((k_query<TF, TM, F, WIDTH, false, R>), blocks, dim3(kBlock), lds, s, A, lds);
+    // with R = 64 four threads to a slot: from 2^30 slots on more than one launch
+    for (uint32_t left = grid, most = tiles_per_launch(kBlock / R * kBlock); left;) {
+        const uint32_t now = left < most ? left : most;
+        const dim3 blocks(now * (kBlock / R));
+        if (pairs) hipLaunchKernelGGL((k_query<TF, TM, F, WIDTH, true, R>), blocks, dim3(kBlock), lds, s, A, lds);
+        else hipLaunchKernelGGL((k_query<TF, TM, F, WIDTH, false, R>), blocks, dim3(kBlock), lds, s, A, lds);
+        A.tile0 += now;
+        left -= now;
+    }
 }
 
 // Rays per block by the launch's slots n.  Fewer rays give more blocks, which fills the chip
