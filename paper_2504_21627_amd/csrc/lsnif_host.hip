@@ -777,7 +777,7 @@ lsnif_status enqueue_query(lsnif_ctx *ctx, const Object &ob, const lsnif_ray *d_
     A.nvox = reinterpret_cast<uint8_t *>(wl);
     A.lists = reinterpret_cast<uint32_t *>(wl + al256(n));
     auto query = [&](const QueryArgs &a, uint32_t g) -> hipError_t {
-        if (gather_sums) return launch_gather_only(a, ob.feat_dtype, ob.F, gather_sums, g, s);
+        if (gather_sums) return launch_gather_only(a, ob.feat_dtype, ob.F, ob.mlp_dtype == LSNIF_FP32, gather_sums, g, s);
         const int L = ob.geom.L;
         if (ob.mlp_dtype == LSNIF_FP32) return launch_query_f32(a, ob.feat_dtype, ob.F, L, false, g, s);
         if (ob.mlp_dtype == LSNIF_FP16) return launch_query_f16(a, ob.feat_dtype, ob.F, L, false, g, s);

@@ -1,6 +1,5 @@
 // Types and device functions the kernels share (gfx950): kernel arguments, the
-// hash-grid encoding, matrix-core operand types, decode, and the walk and
-// gather-ceiling kernels.
+// hash-grid encoding, matrix-core operand types, decode, and the walk kernel.
 #pragma once
 #pragma clang fp contract(off)
 
@@ -399,16 +398,6 @@ __device__ __forceinline__ void fold_max(float *dst, float v)
     if ((threadIdx.x & 63u) == 0) atomicMax(reinterpret_cast<unsigned int *>(dst), __float_as_uint(v));
 }
 
-__device__ __forceinline__ int wave_max(int v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        int u = __shfl_xor(v, o, 64);
-        v = u > v ? u : v;
-    }
-    return v;
-}
-
 // Output heads (Sec. 5.1, 5.3): occlusion logit > 0 is a hit, the hit
 // distance is the sigmoid of its logit over [ta, tb], the normal is the
 // normalised linear head, the material the arg-max logit.
@@ -467,31 +456,6 @@ __device__ __forceinline__ void decode_store(const QueryArgs &A, const Mlp &mm, 
         }
     }
 }
-
-// ------------------------------------------------------------- shared prologue
-//
-// The walk kernels list the voxels of every slot into the workspace; the
-// gather-ceiling kernel then loads each slot's list into LDS
-// and orders the block's rays by voxel count (most first), so that each wave
-// encodes rays with similar numbers of boundary points.  After the prologue,
-// lane `tid` works on ray `src` of the block; its voxel list is at
-// s_list[j * kBlock + src] and its walk state has been reloaded from LDS.
-constexpr int kState = 15;          // words of walk state per ray kept in LDS
-
-struct Shared {
-    float state[kState * kBlock];
-    uint32_t hist[kMaxList + 2];
-    uint16_t perm[kBlock];
-};
-
-struct Lane {
-    VRay w;
-    int nvox;
-    uint32_t src;     // ray index within the block
-    uint32_t r;       // global ray index
-    uint32_t pair;    // pair index (pair queries)
-    bool live;
-};
 
 // Tile of rays (or pairs) this block works on.  The dispatcher deals
 // workgroups to the 8 XCDs in turn (block b runs on XCD b mod 8), each XCD with
@@ -560,78 +524,6 @@ __device__ __forceinline__ void walk_body(const QueryArgs &A, const Geom &g, uin
                           : walk_voxels<RECHECK>(g, w, g.coarse, list, A.n, g.H >> 1);
     }
     if (slot < A.n) A.nvox[slot] = (uint8_t)nvox;
-}
-
-template <bool PAIRS>
-__device__ __forceinline__ void walk_and_sort(const QueryArgs &A, const Geom &g, Shared &S, uint32_t *s_list,
-                                              Lane &L, uint32_t tile)
-{
-    const uint32_t tid = threadIdx.x;
-    const int cap = g.H >> 1;
-    if (tid <= (uint32_t)cap) S.hist[tid] = 0;
-    __syncthreads();
-    const uint32_t slot0 = tile * kBlock + tid;
-    uint32_t r0, pair0;
-    bool live0;
-    VRay w;
-    slot_ray<PAIRS>(A, g, slot0, r0, pair0, live0, w);
-    // the slot's voxel list into LDS, eight loads in flight at a time
-    const int nvox = live0 ? (int)A.nvox[slot0] : 0;
-    const int nmax = __builtin_amdgcn_readfirstlane(wave_max(nvox));
-    for (int j0 = 0; j0 < nmax; j0 += 8) {
-        uint32_t v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (j0 + q < nvox) v[q] = A.lists[(size_t)(j0 + q) * A.n + slot0];
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (j0 + q < nvox) s_list[(j0 + q) * kBlock + tid] = v[q];
-    }
-    float *st = S.state;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        st[(0 + a) * kBlock + tid] = w.o[a];
-        st[(3 + a) * kBlock + tid] = w.d[a];
-        st[(6 + a) * kBlock + tid] = w.inv[a];
-    }
-    st[9 * kBlock + tid] = w.ta;
-    st[10 * kBlock + tid] = w.tb;
-    st[11 * kBlock + tid] = w.tmax;
-    st[12 * kBlock + tid] = __uint_as_float(w.mov | (w.valid ? 8u : 0u) | (w.cand ? 16u : 0u) | ((uint32_t)nvox << 8));
-    st[13 * kBlock + tid] = __uint_as_float(r0);
-    st[14 * kBlock + tid] = __uint_as_float(live0 ? pair0 : 0xffffffffu);
-    const uint32_t pos = atomicAdd(&S.hist[cap - nvox], 1u);
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t acc = 0;
-        for (int b = 0; b <= cap; ++b) {
-            const uint32_t c = S.hist[b];
-            S.hist[b] = acc;
-            acc += c;
-        }
-    }
-    __syncthreads();
-    S.perm[S.hist[cap - nvox] + pos] = (uint16_t)tid;
-    __syncthreads();
-    const uint32_t src = S.perm[tid];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        L.w.o[a] = st[(0 + a) * kBlock + src];
-        L.w.d[a] = st[(3 + a) * kBlock + src];
-        L.w.inv[a] = st[(6 + a) * kBlock + src];
-    }
-    L.w.ta = st[9 * kBlock + src];
-    L.w.tb = st[10 * kBlock + src];
-    L.w.tmax = st[11 * kBlock + src];
-    const uint32_t pk = __float_as_uint(st[12 * kBlock + src]);
-    L.w.mov = pk & 7u;
-    L.w.valid = (pk & 8u) != 0;
-    L.w.cand = (pk & 16u) != 0;
-    L.nvox = (int)(pk >> 8);
-    L.src = src;
-    L.r = __float_as_uint(st[13 * kBlock + src]);
-    L.pair = __float_as_uint(st[14 * kBlock + src]);
-    L.live = PAIRS ? L.pair != 0xffffffffu : tile * kBlock + src < A.n;
 }
 
 // Object of this block's tile: one value for the whole block, read through the
@@ -766,66 +658,6 @@ template <int DW> __device__ __forceinline__ void load_frag(const uint32_t *p, u
         const uint2 x = *reinterpret_cast<const uint2 *>(p);
         d[0] = x.x; d[1] = x.y;
     }
-}
-
-// ------------------------------------------------------------- gather ceiling
-//
-// The query kernel's gathers alone, for measurement: the same prologue (voxel
-// lists from the walk, count sort), the same boundary points, repeated-point
-// reuse and encode_levels batches, but each ray's interpolated features are
-// summed into sums[r] instead of feeding the MLP.  Without the accumulators
-// it runs at the occupancy its gathers and address arithmetic allow, so its
-// time bounds what the query kernel's gathers can take.
-template <typename TF, int F>
-__device__ __forceinline__ void gather_only_body(const QueryArgs &A, float *sums, uint32_t *s_list, Shared &S)
-{
-    constexpr int FP = F == 3 ? 4 : F;
-    constexpr int LPB = 16 / FP;
-    constexpr int NL = (F * sizeof(TF) <= 4 && LPB >= 8) ? 8 : (LPB < 4 ? LPB : 4);
-    const Geom &g = A.g;
-    const TF *__restrict__ tab = reinterpret_cast<const TF *>(A.tables);
-    Lane ln;
-    walk_and_sort<false>(A, g, S, s_list, ln, block_tile(A.tile0));
-    const int count = 2 * ln.nvox;
-    const int wmax = __builtin_amdgcn_readfirstlane(wave_max(count));
-    float total = 0.0f, prev = 0.0f;
-    uint32_t pp[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu};
-    int pface = -1;
-    for (int h = 0; h < wmax; ++h) {
-        float p[3] = {0.0f, 0.0f, 0.0f};
-        int face = 0;
-        const bool has = h < count;
-        if (has) face = boundary_point(ln.w, s_list[(h >> 1) * kBlock + ln.src], h & 1, p);
-        const bool dup = has && (h & 1) == 0 && face == pface && __float_as_uint(p[0]) == pp[0] &&
-                         __float_as_uint(p[1]) == pp[1] && __float_as_uint(p[2]) == pp[2];
-        float here = 0.0f;
-        if (has && !dup) {
-            for (int l0 = 0; l0 < g.L; l0 += NL) {
-                float v[NL][F];
-                encode_levels<TF, F, NL>(g, tab, l0, p, face, v);
-#pragma unroll
-                for (int lv = 0; lv < NL; ++lv)
-#pragma unroll
-                    for (int f = 0; f < F; ++f) here += v[lv][f];
-            }
-        } else if (dup) {
-            here = prev;
-        }
-        total += here;
-        prev = here;
-#pragma unroll
-        for (int b = 0; b < 3; ++b) pp[b] = __float_as_uint(p[b]);
-        pface = has ? face : -1;
-    }
-    if (ln.live) sums[ln.r] = total;
-}
-
-template <typename TF, int F>
-__global__ __launch_bounds__(kBlock) void k_gather_only(QueryArgs A, float *sums)
-{
-    extern __shared__ uint32_t s_list[];
-    __shared__ Shared S;
-    gather_only_body<TF, F>(A, sums, s_list, S);
 }
 
 // ------------------------------------------------------------------ broad phase

@@ -52,8 +52,9 @@ hipError_t launch_query_fp8(const QueryArgs &A, int feat_dtype, int F, int max_L
 // largest grid of its objects.
 hipError_t launch_walk(const QueryArgs &A, bool pairs, bool recheck, uint32_t max_V, uint32_t grid, hipStream_t s);
 hipError_t launch_debug(const DebugArgs &D, hipStream_t s);
-// Gather ceiling: the query's gathers alone, each ray's feature sum into sums[r].
-hipError_t launch_gather_only(const QueryArgs &A, int feat_dtype, int F, float *sums, uint32_t grid, hipStream_t s);
+// Gather ceiling: the query's gathers alone, each ray's feature sum into sums[r]; f32: the MLP's type is.
+hipError_t launch_gather_only(const QueryArgs &A, int feat_dtype, int F, bool f32, float *sums, uint32_t grid,
+                              hipStream_t s);
 // Broad phase: the exclusive scan of the pairs per ray into B.offsets (their total at
 // offsets[n_rays]), then the pairs themselves.
 struct BroadArgs;

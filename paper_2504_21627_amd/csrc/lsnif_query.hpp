@@ -74,6 +74,62 @@ template <int R> __device__ __forceinline__ uint32_t block_subtile(uint32_t tile
     return first + ((k / C) * 8u + x) * C + k % C;
 }
 
+// The boundary points of voxels j0 .. j0 + nj - 1 of a tile's rays, by all of a block: the distinct ones,
+// packed, into pts (their number into S.npts), and for point h of ray i its place there into
+// smap[h R + i]: `zero` past the ray's list, kSameSlot where it repeats the point before it.
+template <int R>
+__device__ __forceinline__ void pack_points(const QueryArgs &A, uint32_t slot0, uint32_t j0, uint32_t nj, uint32_t zero,
+                                            QueryShared<R> &S, float4 *pts, uint16_t *smap)
+{
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) S.npts = 0u;
+    __syncthreads();
+    for (uint32_t i0 = wave * 64u; i0 < nj * R; i0 += kBlock) {
+        const uint32_t jj = (i0 + lane) / R, j = j0 + jj, ray = (i0 + lane) % R;
+        const bool has = jj < nj && j < S.nvox[ray];
+        float p0[3] = {}, p1[3] = {};
+        int f0 = 0, f1 = 0;
+        bool dup = false;
+        if (has) {
+            VRay v;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                v.o[a] = S.ray[a][ray];
+                v.d[a] = S.ray[3 + a][ray];
+                v.inv[a] = S.ray[6 + a][ray];
+            }
+            v.mov = S.mov[ray];
+            const uint32_t *list = A.lists + slot0 + ray;
+            const uint32_t c = list[(size_t)j * A.n];
+            f0 = boundary_point(v, c, false, p0);
+            f1 = boundary_point(v, c, true, p1);
+            if (jj > 0u) {
+                // the entry point is often the exit point of the voxel before it
+                float q[3];
+                const int fq = boundary_point(v, list[(size_t)(j - 1u) * A.n], true, q);
+                dup = fq == f0 && __float_as_uint(q[0]) == __float_as_uint(p0[0]) &&
+                      __float_as_uint(q[1]) == __float_as_uint(p0[1]) &&
+                      __float_as_uint(q[2]) == __float_as_uint(p0[2]);
+            }
+        }
+        const uint64_t m_in = __ballot(has && !dup), m_out = __ballot(has);
+        const uint32_t n_in = (uint32_t)__builtin_popcountll(m_in);
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&S.npts, n_in + (uint32_t)__builtin_popcountll(m_out));
+        base = __builtin_amdgcn_readfirstlane(base);
+        const uint64_t below = (1ull << lane) - 1ull;
+        const uint32_t s0 = base + (uint32_t)__builtin_popcountll(m_in & below);
+        const uint32_t s1 = base + n_in + (uint32_t)__builtin_popcountll(m_out & below);
+        if (jj < nj) {
+            smap[(2u * jj) * R + ray] = (uint16_t)(has ? (dup ? kSameSlot : s0) : zero);
+            smap[(2u * jj + 1u) * R + ray] = (uint16_t)(has ? s1 : zero);
+        }
+        if (has && !dup) pts[s0] = make_float4(p0[0], p0[1], p0[2], __int_as_float(f0));
+        if (has) pts[s1] = make_float4(p1[0], p1[1], p1[2], __int_as_float(f1));
+    }
+    __syncthreads();
+}
+
 // One block answers a tile of R slots whose voxel lists the walk has written.
 //
 // The encoding's gathers bound the kernel, so what matters is that every lane of every
@@ -194,52 +250,7 @@ __device__ __forceinline__ void query_body(const QueryArgs &A, const Geom &g, co
     for (uint32_t j0 = 0; j0 < most; j0 += vox) {
         const uint32_t nj = min(vox, most - j0);
         // ---- points of voxels j0 .. j0 + nj - 1: the distinct ones, packed
-        if (tid == 0) S.npts = 0u;
-        __syncthreads();
-        for (uint32_t i0 = wave * 64u; i0 < nj * R; i0 += NT) {
-            const uint32_t jj = (i0 + lane) / R, j = j0 + jj, ray = (i0 + lane) % R;
-            const bool has = jj < nj && j < S.nvox[ray];
-            float p0[3] = {}, p1[3] = {};
-            int f0 = 0, f1 = 0;
-            bool dup = false;
-            if (has) {
-                VRay v;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    v.o[a] = S.ray[a][ray];
-                    v.d[a] = S.ray[3 + a][ray];
-                    v.inv[a] = S.ray[6 + a][ray];
-                }
-                v.mov = S.mov[ray];
-                const uint32_t *list = A.lists + slot0 + ray;
-                const uint32_t c = list[(size_t)j * A.n];
-                f0 = boundary_point(v, c, false, p0);
-                f1 = boundary_point(v, c, true, p1);
-                if (jj > 0u) {
-                    // the entry point is often the exit point of the voxel before it
-                    float q[3];
-                    const int fq = boundary_point(v, list[(size_t)(j - 1u) * A.n], true, q);
-                    dup = fq == f0 && __float_as_uint(q[0]) == __float_as_uint(p0[0]) &&
-                          __float_as_uint(q[1]) == __float_as_uint(p0[1]) &&
-                          __float_as_uint(q[2]) == __float_as_uint(p0[2]);
-                }
-            }
-            const uint64_t m_in = __ballot(has && !dup), m_out = __ballot(has);
-            const uint32_t n_in = (uint32_t)__builtin_popcountll(m_in);
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&S.npts, n_in + (uint32_t)__builtin_popcountll(m_out));
-            base = __builtin_amdgcn_readfirstlane(base);
-            const uint64_t below = (1ull << lane) - 1ull;
-            const uint32_t s0 = base + (uint32_t)__builtin_popcountll(m_in & below);
-            const uint32_t s1 = base + n_in + (uint32_t)__builtin_popcountll(m_out & below);
-            if (jj < nj) {
-                smap[(2u * jj) * R + ray] = (uint16_t)(has ? (dup ? kSameSlot : s0) : zero);
-                smap[(2u * jj + 1u) * R + ray] = (uint16_t)(has ? s1 : zero);
-            }
-            if (has && !dup) pts[s0] = make_float4(p0[0], p0[1], p0[2], __int_as_float(f0));
-            if (has) pts[s1] = make_float4(p1[0], p1[1], p1[2], __int_as_float(f1));
-        }
-        __syncthreads();
+        pack_points<R>(A, slot0, j0, nj, zero, S, pts, smap);
         // whether some first-layer weight is not finite; training moves those of FP32 on the device
         uint32_t odd = mm.odd;
         if constexpr (f32) odd = *(cword *)mm.odd_at;   // through the scalar path, needed after the features
@@ -638,13 +649,18 @@ inline void query_go(QueryArgs A, int max_L, bool pairs, uint32_t grid, hipStrea
 // 256 rays 20 / 27 / 36, 6,000 42 / 43 / 65, 39,999 102 / 115 / 133, 600,000 826 / 750 / 807,
 // 2,097,152 2,250 / 1,887 / 1,706 (16 levels, FP16); 60,000 rays with 8 levels of 64 KiB
 // 72 / 55 / 50; 60,000 and 524,288 in float32 356 / 297 / 329 and 1,934 / 1,338 / 1,236.
+inline int rays_per_block(uint32_t n, uint32_t batches, bool f32)
+{
+    const uint32_t mid = batches <= 2u ? 32768u : (f32 ? 393216u : 786432u);
+    return n <= 8192u ? 16 : (n <= mid ? 32 : 64);
+}
+
 template <typename TF, typename TM, int F, int WIDTH>
 inline void query_rays(const QueryArgs &A, int max_L, bool pairs, uint32_t grid, hipStream_t s)
 {
-    const uint32_t n = grid * kBlock;
-    const uint32_t mid = level_batches<TM, F>(max_L) <= 2u ? 32768u : (PointT<TM, F>::f32 ? 393216u : 786432u);
-    if (n <= 8192u) query_go<TF, TM, F, WIDTH, 16>(A, max_L, pairs, grid, s);
-    else if (n <= mid) query_go<TF, TM, F, WIDTH, 32>(A, max_L, pairs, grid, s);
+    const int R = rays_per_block(grid * kBlock, level_batches<TM, F>(max_L), PointT<TM, F>::f32);
+    if (R == 16) query_go<TF, TM, F, WIDTH, 16>(A, max_L, pairs, grid, s);
+    else if (R == 32) query_go<TF, TM, F, WIDTH, 32>(A, max_L, pairs, grid, s);
     else query_go<TF, TM, F, WIDTH, 64>(A, max_L, pairs, grid, s);
 }
 
