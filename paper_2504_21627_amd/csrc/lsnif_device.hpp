@@ -463,8 +463,9 @@ __device__ __forceinline__ void find_voxels(const Geom &g, const VRay &w, int la
 }
 
 // walk_voxels by one lane, cell by cell: for rays that meet many voxels, whose list
-// is full after a few cells.  (walk_voxels itself keeps part of its state in
-// scratch memory, and a kernel with scratch takes 10 us longer to start.)
+// is full after a few cells, so that entering bricks gains nothing (us, walk_voxels here
+// and this: 40,000 rays, 90 % of V = 32 occupied 56 and 53, 30 % of V = 128 147 and 130, 20 %
+// of V = 256 248 and 218).
 template <bool RECHECK>
 __device__ __forceinline__ int walk_cells(const Geom &g, const VRay &w, const WalkStart &S, uint32_t *list,
                                           uint32_t stride, int cap)
