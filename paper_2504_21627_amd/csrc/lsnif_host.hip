@@ -472,7 +472,6 @@ lsnif_status lsnif_build(lsnif_ctx *ctx, const lsnif_object_desc *d, uint32_t *o
     m.n_mat = d->n_mat;
     m.has_albedo = d->has_albedo ? 1 : 0;
     m.kb_point = KB;
-    m.fp = d->F == 3 ? 4 : d->F;
     const uint32_t id = ctx->next_id++;
     ctx->objects[id] = ob;
     ctx->used += ob.bytes;
@@ -806,7 +805,6 @@ lsnif_status upload_table(lsnif_ctx *ctx, uint32_t &n_objs)
         d.m = kv.second.mlp;
         d.tables = kv.second.d_tab;
         d.live = 1;
-        d.kb_point = kv.second.mlp.kb_point;
     }
     const size_t bytes = t.size() * sizeof(ObjDev);
     // earlier queries may still read the old table

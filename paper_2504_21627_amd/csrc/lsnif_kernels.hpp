@@ -27,7 +27,6 @@ struct Mlp {
     float slope;
     int32_t n_mat, has_albedo;
     int32_t kb_point;         // matrix-core path: K blocks (16 wide) per boundary point
-    int32_t fp;               // matrix-core path: features per level after padding
     uint32_t odd;             // matrix-core path: not 0 if some first-layer weight is not finite
     uint32_t *odd_at;         // float32 path: the same, kept after the weights, which training moves
     const float *odd_w;       // then: the first layer as [inputs][width], read for those weights
@@ -57,7 +56,6 @@ struct ObjDev {
     Mlp m;
     const void *tables;
     int32_t live;
-    int32_t kb_point;
 };
 
 struct PairArgs {
@@ -619,25 +617,6 @@ __device__ __forceinline__ void pack8(const float *v, float scale, uint32_t *d)
     } else {
 #pragma unroll
         for (int q = 0; q < 4; ++q) d[q] = pack2<TM>(v[2 * q], v[2 * q + 1]);
-    }
-}
-
-// Value e (0..7) of a packed fragment, widened to float (not rescaled).
-template <typename TM> __device__ __forceinline__ float unpack8(const uint32_t *d, int e)
-{
-    if constexpr (MmaT<TM>::scaled) {
-        const uint32_t w = d[e >> 2];
-        switch (e & 3) {
-        case 0: return __builtin_amdgcn_cvt_f32_fp8((int)w, 0);
-        case 1: return __builtin_amdgcn_cvt_f32_fp8((int)w, 1);
-        case 2: return __builtin_amdgcn_cvt_f32_fp8((int)w, 2);
-        default: return __builtin_amdgcn_cvt_f32_fp8((int)w, 3);
-        }
-    } else {
-        const uint16_t u = (uint16_t)((e & 1) ? (d[e >> 1] >> 16) : (d[e >> 1] & 0xffffu));
-        TM v;
-        __builtin_memcpy(&v, &u, 2);
-        return (float)v;
     }
 }
 
