@@ -43,8 +43,8 @@ struct Geom {
     uint32_t dense_mask;      // bit l: level l indexed directly ((R+1)^3 <= T)
     uint32_t aligned_mask;    // bit l: R % V == 0, the crossing-axis weight is 0 or 1
     uint32_t recheck;         // 1: grazing voxels of the walk are re-decided in float64
-    uint32_t sort_bits;       // coherence sort of single-object batches: 2^bits cells per axis (0 = no sort, <= 6)
-    uint32_t pair_bits;       // grouping of pairs within an object: 2^bits cells per axis (<= 5)
+    uint32_t sort_bits;       // coherence sort of single-object batches: 2^bits cells per axis (0 = no sort, <= 7)
+    uint32_t pair_bits;       // grouping of pairs within an object: 2^bits cells per axis (1..6)
     int32_t R[kMaxLevels];
     float lsc[kMaxLevels];    // (float)R / (float)V
     uint32_t my[kMaxLevels], mz[kMaxLevels], dmask[kMaxLevels], hmask[kMaxLevels];

@@ -501,7 +501,7 @@ __device__ __forceinline__ void slot_ray(const QueryArgs &A, const Geom &g, uint
 
 // The voxel walk of every slot, in a kernel of its own: it needs few registers,
 // so many waves per SIMD hide the latency of its dependent brick-mask loads,
-// which the query kernels (two waves per SIMD) could not.
+// which the query kernels (four waves per SIMD, each with gathers of its own to wait for) could not.
 template <bool PAIRS, bool RECHECK>
 __device__ __forceinline__ void walk_body(const QueryArgs &A, const Geom &g, uint32_t *coarse)
 {

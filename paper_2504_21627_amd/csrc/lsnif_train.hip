@@ -2,6 +2,10 @@
 // products, the losses, the backward layer products, the scatter of the
 // encoding's gradient onto the tables, and Adam over every parameter.
 //
+// What lies between the walk and Adam is one kernel for objects and batches that
+// step_takes accepts (at most 36 blocks of weight gradient; with more than 128 inputs,
+// 4,096 rays and more), and launches of their own for the others.
+//
 // The parameters are the FP32 object's own device buffers: the tables
 // [L][T][F] and the weights in the FP32 query kernel's layout, each layer
 // stored as [in][ld] (ld = width for hidden layers, kMaxOut for the head, the
