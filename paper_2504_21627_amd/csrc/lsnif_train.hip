@@ -15,9 +15,11 @@
 // The table gradient is accumulated with float atomics into several copies
 // (one per XCD when memory allows; contention on the entries many rays reach
 // is what bounds the scatter), summed into the first copy at the end.  Weight
-// gradients go through per-chunk partial products and a sum, no atomics.
+// gradients go through partial products (per chunk of rays, or per block of the one
+// kernel) and a sum, no atomics.
 //
-// Activations of the backward pass overwrite the forward ones layer by layer:
+// Activations of the backward pass overwrite the forward ones layer by layer (in the one
+// kernel, in LDS):
 // a layer's input is read for its weight gradient, then replaced by the
 // gradient with respect to it (the derivative epilogue reads each element
 // before the same thread writes it), and the encoding buffer finally holds
