@@ -710,8 +710,8 @@ def bench_c2(L, args):
             L.lsnif_set_tuning(ctx, oid, *tuning.values())
         ub_ms = None
         if name == "fp16":
-            # the gather ceiling: the same batch through the kernel that only gathers (SURVEY's
-            # ub_gather), with the walk of the whole batch first as for the roofline's kernel time
+            # the gather ceiling: the same batch through the kernel that only gathers, with the
+            # walk of the whole batch first as for the roofline's kernel time
             L.lsnif_set_tuning(ctx, oid, *iso.values())
             sums = torch.empty(n, dtype=torch.float32, device="cuda")
             _, _, _, _, ub_ms = time_calls(L, ctx, lambda st: L.lsnif_gather_ceiling(ctx, oid, rays, sums, st),
